@@ -195,8 +195,11 @@ def main():
     roofline = {
         "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": round(achieved / HBM_PEAK_GBS, 4),
-        "traffic": stored_traffic("k_iter_pm2") if fused and args.msg_dtype == "f32" else None,
-        "kernel": (f"k_iter_pm2 level-0 fused pair of checkerboard half-sweeps ({w}x{h}x{L}, {args.msg_dtype} "
+        "traffic": stored_traffic("k_iter_pm2") if fused and lv_units[0] <= 2.5 * w * h * L and args.msg_dtype == "f32"
+        else None,
+        "kernel": (f"k_iter_stream level-0 launches of several pairs of checkerboard half-sweeps ({w}x{h}x{L}, "
+                   f"{args.msg_dtype} messages)") if lv_units[0] > 2.5 * w * h * L else
+                  (f"k_iter_pm2 level-0 fused pair of checkerboard half-sweeps ({w}x{h}x{L}, {args.msg_dtype} "
                    "messages)") if fused else
                   f"k_iter_pm level-0 checkerboard half-sweep ({w}x{h}x{L}, {args.msg_dtype} messages)",
         "avg_launch_us": round(l0_ms * 1e3, 2), "launches_per_step": lv_n[0],

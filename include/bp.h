@@ -95,7 +95,8 @@ typedef struct {
                                   whose contents only bp_backward interprets */
     int32_t variant;           /* 0 = library choice: pixel-major levels with K >= 2 run two
                                   half-sweeps per launch (tiles whose colour-1 messages stay
-                                  on chip between the two; a second buffer of half a level's
+                                  on chip between the two), large ones four or six (streamed
+                                  down strips of columns; a second buffer of half a level's
                                   messages in the workspace), also when checkpoints are saved
                                   every even number of half-sweeps; with count > 1 when K is
                                   even and every level of every problem does so (one launch
@@ -336,9 +337,10 @@ typedef struct {
     double bytes;           /* algorithmic memory traffic of the covered launches, per pixel and
                                label of the level (mb = msg_bytes): a single half-sweep
                                (4 + 8 mb) / 2 (the active half reads its cost and four incoming
-                               rows and writes four outgoing ones); a fused pair 4 + 4 mb (both
-                               colours' costs, colour 0's rows read and written), plus 2 mb
-                               for a pair that ends a level and stores colour 1's rows */
+                               rows and writes four outgoing ones); a launch of one or more fused
+                               pairs 4 + 4 mb (both colours' costs, colour 0's rows read and
+                               written once), plus 2 mb when it ends a level and stores colour
+                               1's rows */
 } bp_launch_record;
 
 /*

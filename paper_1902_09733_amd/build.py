@@ -31,6 +31,9 @@ EXTRA = {
     "bp_iter_pm2_f32.hip": ["-fno-honor-nans"],
     "bp_iter_pm2_f16.hip": ["-fno-honor-nans"],
     "bp_iter_pm2_bf16.hip": ["-fno-honor-nans"],
+    "bp_iter_stream_f32.hip": ["-fno-honor-nans"],
+    "bp_iter_stream_f16.hip": ["-fno-honor-nans"],
+    "bp_iter_stream_bf16.hip": ["-fno-honor-nans"],
 }
 
 
@@ -57,7 +60,7 @@ def _compile(src: str, verbose: bool) -> str:
 def build(verbose: bool = False, jobs: int | None = None) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = sources()
-    jobs = jobs or min(len(srcs), max(1, (os.cpu_count() or 4) // 2))
+    jobs = jobs or min(len(srcs), os.cpu_count() or 4)
     with cf.ThreadPoolExecutor(jobs) as ex:
         objs = list(ex.map(lambda s: _compile(s, verbose), srcs))
     tmp = LIB + ".tmp"

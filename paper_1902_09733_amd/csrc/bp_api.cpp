@@ -291,31 +291,32 @@ bp_status run_one(const bp_problem &q, const Plan &pl, const bp_params &p, uint8
         const bool lpairs = level_pairs(pl, l, K);
         const int variant = lpairs ? 1 : pl.variant;
         if (lpairs) {
-            // Fused pairs over half-sweeps [t0, K - (K & 1)).  Phase 1 of the
-            // first pair reads the parent's state, zeros (coarsest level) or the
-            // level's own state after a materialised parent copy; pairs
-            // alternate between the level's colour-0 block and the second
-            // buffer so that the last one writes the level's own block.  When
-            // the first pair would have to read and write the own block, two
-            // single half-sweeps go first.
+            // Fused pairs over half-sweeps [t0, K - (K & 1)), one or several per
+            // launch.  The first launch reads the parent's state, zeros
+            // (coarsest level) or the level's own state after a materialised
+            // parent copy; launches alternate between the level's colour-0
+            // block and the second buffer so that the last one writes the
+            // level's own block.  When the first would have to read and write
+            // the own block, two single half-sweeps go first.
             const size_t own = pl.lv[l].msg_off, other = pl.y_off;
-            int np = K / 2;
             const bool own_src = l < n - 1 && !first_src;
-            if (own_src && (np & 1)) {
+            PairSchedule sched = pair_schedule(pl, l, K / 2, p.tau, ckpt != nullptr, own_src);
+            if (own_src && (sched.count() & 1)) {
                 for (; t0 < 2; ++t0, ++launches) {
                     if ((st = launch_iteration(pl, l, t0, 0, p.lambda, p.tau, nullptr, variant, ws, s)) != BP_OK)
                         return st;
                     lbytes += sweep_bytes(pl, l);
                 }
-                --np;
+                --sched.ones;
             }
+            const int np = sched.count();   // launches
             size_t src_off = own;
             // Checkpoints (finest level only): out-of-grid slots of every saved
             // state are zeroed once, the pairs write the in-grid rows.
             const size_t ck_state = pl.lv[0].msg_bytes;
             const int ck_n = ckpt ? checkpoint_states(K, p.checkpoint_every) : 0;
             if (ckpt && (st = launch_zero_borders(&pl, &ckpt, 1, ck_n, s)) != BP_OK) return st;
-            for (int pi = 0; pi < np; ++pi, t0 += 2, ++launches) {
+            for (int pi = 0; pi < np; t0 += 2 * sched.pairs(pi), ++pi, ++launches) {
                 const size_t dst_off = ((np - 1 - pi) & 1) ? other : own;
                 int kind = PAIR_SRC_OWN;
                 if (t0 == 0) kind = l == n - 1 ? PAIR_SRC_ZERO : (first_src ? PAIR_SRC_PARENT : PAIR_SRC_OWN);
@@ -330,7 +331,7 @@ bp_status run_one(const bp_problem &q, const Plan &pl, const bp_params &p, uint8
                 // `every` half-sweeps, and whole at the end.
                 uint8_t *ck = nullptr;
                 if (ckpt) {
-                    const int tn = t0 + 2;
+                    const int tn = t0 + 2;   // one pair per launch when states are saved
                     if (ends) ck = ckpt + (size_t)(ck_n - 1) * ck_state;
                     else if (tn % p.checkpoint_every == 0 && tn < K)
                         ck = ckpt + (size_t)(tn / p.checkpoint_every - 1) * ck_state;
@@ -339,7 +340,7 @@ bp_status run_one(const bp_problem &q, const Plan &pl, const bp_params &p, uint8
                 if (rec && hipEventRecord(prof->ev[prof->n][0], s) != hipSuccess) return BP_ERR_HIP;
                 if ((st = launch_iteration_pair(pl, l, kind, src_off, dst_off, store_c1, p.lambda, p.tau,
                                                 rd ? q.disparity : nullptr, ws, s, ck, ends,
-                                                rd ? q.soft_disparity : nullptr, inv_t)) != BP_OK)
+                                                rd ? q.soft_disparity : nullptr, inv_t, sched.pairs(pi))) != BP_OK)
                     return st;
                 if (rec) {
                     if (hipEventRecord(prof->ev[prof->n][1], s) != hipSuccess) return BP_ERR_HIP;
@@ -349,7 +350,7 @@ bp_status run_one(const bp_problem &q, const Plan &pl, const bp_params &p, uint8
                     r.launches = 1;
                     r.readout_fused = rd;
                     r.msg_bytes = fmt_bytes(pl.lv[l].fmt);
-                    r.units = 2.0 * pl.lv[l].w * pl.lv[l].h * pl.L;
+                    r.units = 2.0 * sched.pairs(pi) * pl.lv[l].w * pl.lv[l].h * pl.L;
                     r.ms = 0.0f;
                     r.bytes = pair_bytes(pl, l, store_c1);
                 }
@@ -491,13 +492,21 @@ bool plan_run(const bp_problem *probs, int32_t count, const bp_params *p, Plan *
         }
         if (!pairs && !plan_all(probs, count, p, plans, total)) return false;
         if (table) *table = batch_table_bytes(count, p->levels, p->iters_per_level, pairs);
-        // A batched launch covers several problems with one kernel, so their
-        // finest levels share the cost storage: the narrowest every problem's
-        // costs allow (bytes are exact in FP16 too), and FP32 for the
-        // one-half-sweep kernels.
-        int cf = pairs ? COST_U8 : COST_F32;
-        for (int i = 0; i < count; ++i) cf = std::min(cf, plans[i].lv[0].cost_fmt);
-        for (int i = 0; i < count; ++i) plans[i].lv[0].cost_fmt = cf;
+        // A batched launch covers several problems of one lane split with one
+        // kernel, so their finest levels share the cost storage: the narrowest
+        // every such problem's costs allow (bytes are exact in FP16 too), and
+        // FP32 for the one-half-sweep kernels.
+        for (int i = 0; i < count; ++i) {
+            int S, R, Sj, Rj;
+            pm_split(plans[i].L, &S, &R);
+            int cf = pairs ? COST_U8 : COST_F32;
+            for (int j = 0; j < count; ++j) {
+                pm_split(plans[j].L, &Sj, &Rj);
+                // Entries before i already hold their split's shared format.
+                if (Sj == S && Rj == R) cf = std::min(cf, plans[j].lv[0].cost_fmt);
+            }
+            plans[i].lv[0].cost_fmt = cf;
+        }
     }
     return true;
 }
@@ -572,6 +581,11 @@ bp_status run_batched_pairs(const bp_problem *probs, int32_t count, const Plan *
     // still survives from one pair to the next (measured on 48 problems of
     // 60 MB to 2 GB: letting all those above the budget share launches was
     // 1-3% slower than one after the other).
+    // A problem whose pairs run several per launch is a group of its own, too.
+    auto schedule_of = [&](int l, int i) {
+        const bool own_src = l < n - 1 && plans[i].lv[l].fmt != plans[i].lv[l + 1].fmt;
+        return pair_schedule(plans[i], l, np, p.tau, ckpt != nullptr, own_src);
+    };
     int *grp = new int[(size_t)n * count], ng = 1;
     for (int l = 0; l < n; ++l) {
         int g = 0;
@@ -579,11 +593,12 @@ bp_status run_batched_pairs(const bp_problem *probs, int32_t count, const Plan *
         for (int i = 0; i < count; ++i) {
             const Level &v = plans[i].lv[l];
             const size_t wsz = v.cost_bytes + v.msg_bytes + (size_t)4 * v.blk * fmt_bytes(v.fmt);
-            if (acc > 0 && acc + wsz > kPairGroupBytes) {
+            const bool alone = schedule_of(l, i).count() < np;
+            if (acc > 0 && (alone || acc + wsz > kPairGroupBytes)) {
                 ++g;
                 acc = 0;
             }
-            acc += wsz;
+            acc += alone ? kPairGroupBytes : wsz;
             grp[(size_t)l * count + i] = g;
         }
         if (g + 1 > ng) ng = g + 1;
@@ -610,14 +625,19 @@ bp_status run_batched_pairs(const bp_problem *probs, int32_t count, const Plan *
                     for (int i = 0; i < count; ++i) {
                         if (cls_of[i] != c || grp[(size_t)l * count + i] != g) continue;
                         const Plan &pl = plans[i];
+                        // Launch q of nl (a group of several problems runs one
+                        // pair per launch).
+                        const PairSchedule sched = schedule_of(l, i);
+                        const int nl = sched.count();
+                        if (q >= nl) continue;
                         const bool fusable = l == n - 1 || pl.lv[l].fmt == pl.lv[l + 1].fmt;
                         const size_t own = pl.lv[l].msg_off, other = pl.y_off;
-                        const size_t dst = ((np - 1 - q) & 1) ? other : own;
-                        const size_t src = q == 0 ? own : (((np - q) & 1) ? other : own);
+                        const size_t dst = ((nl - 1 - q) & 1) ? other : own;
+                        const size_t src = q == 0 ? own : (((nl - q) & 1) ? other : own);
                         const int kind = q > 0 ? PAIR_SRC_OWN
                                                : (l == n - 1 ? PAIR_SRC_ZERO
                                                              : (fusable ? PAIR_SRC_PARENT : PAIR_SRC_OWN));
-                        const bool ends = q == np - 1;
+                        const bool ends = q == nl - 1;
                         const bool rd = l == 0 && ends && fuse[i];
                         // State after the pair (finest level): saved every
                         // `every` half-sweeps and at the end.
@@ -638,7 +658,7 @@ bp_status run_batched_pairs(const bp_problem *probs, int32_t count, const Plan *
                         pe.a = make_pair_args(pl, l, kind, src, dst, store_c1, p.lambda, p.tau,
                                               rd ? probs[i].disparity : nullptr, ws, ck, ends,
                                               rd ? probs[i].soft_disparity : nullptr,
-                                              probs[i].soft_disparity ? 1.0f / p.temperature : 0.0f);
+                                              probs[i].soft_disparity ? 1.0f / p.temperature : 0.0f, sched.pairs(q));
                         pe.block0 = b0;
                         b0 += pair_blocks(pe.a);
                         const size_t lb = pair_lds_bytes(pe.a.tx, pe.a.ty, (int)pe.a.lp, fmt_bytes(pl.lv[l].fmt));
@@ -679,7 +699,9 @@ bp_status run_batched_pairs(const bp_problem *probs, int32_t count, const Plan *
                     if (num[slot] == 0) continue;
                     // A lone problem takes the one-problem kernel (labels
                     // without padding skip the padded-label masks).
-                    if (num[slot] == 1)
+                    if (num[slot] == 1 && host[start[slot]].a.pairs > 1)
+                        st = dispatch_iter_stream(host[start[slot]].a, fmt, cls_S[c], cls_R[c], s);
+                    else if (num[slot] == 1)
                         st = dispatch_iter_pm2(host[start[slot]].a, fmt, cls_S[c], cls_R[c], ro[slot], s);
                     else
                         st = launch_iteration_pair_batch(dev + start[slot], num[slot], blocks[slot], lds[slot], fmt,

@@ -489,7 +489,7 @@ IterArgs make_iter_args(const Plan &p, int l, int t, int src_mode, float lambda,
     a.ncomp = v.h * v.wh;
     a.lambda = lambda;
     a.lt = lambda * tau;
-    a.near = tau <= 2.0f ? 1 : tau <= 3.0f ? 2 : 0;
+    a.near = near_window(tau);
     return a;
 }
 
@@ -509,7 +509,7 @@ bp_status launch_iteration(const Plan &p, int l, int t, int src_mode, float lamb
 
 PairArgs make_pair_args(const Plan &p, int l, int src_kind, size_t src_off, size_t dst_off, bool write_c1,
                         float lambda, float tau, int32_t *disp, uint8_t *ws, uint8_t *ck, bool ck_c1, float *soft,
-                        float inv_t)
+                        float inv_t, int pairs)
 {
     const Level &v = p.lv[l];
     PairArgs a;
@@ -548,12 +548,19 @@ PairArgs make_pair_args(const Plan &p, int l, int src_kind, size_t src_off, size
     a.L = p.L;
     a.lambda = lambda;
     a.lt = lambda * tau;
-    a.near = tau <= 2.0f ? 1 : tau <= 3.0f ? 2 : 0;
+    a.near = near_window(tau);
     a.cost_fmt = v.cost_fmt;
-    pair_tile(v.lp, fmt_bytes(v.fmt), v.w, v.h, &a.tx, &a.ty);
-    a.tiles_x = (v.w + a.tx - 1) / a.tx;
-    a.ntiles = a.tiles_x * ((v.h + a.ty - 1) / a.ty);
-    a.per_xcd = (a.ntiles + 7) / 8;
+    a.pairs = pairs;
+    if (pairs > 1) {
+        int S, R;
+        pm_split(p.L, &S, &R);
+        stream_shape(&a, S, R);
+    } else {
+        pair_tile(v.lp, fmt_bytes(v.fmt), v.w, v.h, &a.tx, &a.ty);
+        a.tiles_x = (v.w + a.tx - 1) / a.tx;
+        a.ntiles = a.tiles_x * ((v.h + a.ty - 1) / a.ty);
+        a.per_xcd = (a.ntiles + 7) / 8;
+    }
     a.ck = ck;
     a.ck_bytes = ck ? (uint32_t)v.msg_bytes : 0u;
     a.ck_c1 = ck != nullptr && ck_c1;
@@ -562,12 +569,13 @@ PairArgs make_pair_args(const Plan &p, int l, int src_kind, size_t src_off, size
 
 bp_status launch_iteration_pair(const Plan &p, int l, int src_kind, size_t src_off, size_t dst_off, bool write_c1,
                                 float lambda, float tau, int32_t *disp, uint8_t *ws, hipStream_t s, uint8_t *ck,
-                                bool ck_c1, float *soft, float inv_t)
+                                bool ck_c1, float *soft, float inv_t, int pairs)
 {
-    const PairArgs a =
-        make_pair_args(p, l, src_kind, src_off, dst_off, write_c1, lambda, tau, disp, ws, ck, ck_c1, soft, inv_t);
+    const PairArgs a = make_pair_args(p, l, src_kind, src_off, dst_off, write_c1, lambda, tau, disp, ws, ck, ck_c1,
+                                      soft, inv_t, pairs);
     int S, R;
     pm_split(p.L, &S, &R);
+    if (pairs > 1) return dispatch_iter_stream(a, p.lv[l].fmt, S, R, s);
     return dispatch_iter_pm2(a, p.lv[l].fmt, S, R, disp != nullptr || soft != nullptr, s);
 }
 

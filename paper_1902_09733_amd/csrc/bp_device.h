@@ -393,6 +393,26 @@ __device__ __forceinline__ void seg_near2(float (&e)[4], float &m, float b0, flo
     }
 }
 
+// The exchanges of the five-label form with the scans' roundings over a whole
+// 16-lane row, interleaved like row_scans16: p receives `below` of the next
+// lower lane and q `above` of the next higher lane (a lane at the row's edge
+// keeps what p and q hold), and m becomes the row's minimum.
+__device__ __forceinline__ void row_shift16(float &p, float &q, float &m, float below, float above)
+{
+    asm volatile("s_nop 1\n\t"
+                 "v_min_f32_dpp %2, %2, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+                 "v_mov_b32_dpp %0, %3 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_mov_b32_dpp %1, %4 row_shl:1 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_min_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+                 "s_nop 1\n\t"
+                 "v_min_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+                 "s_nop 1\n\t"
+                 "v_min_f32_dpp %2, %2, %2 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+                 "s_nop 1"
+                 : "+v"(p), "+v"(q), "+v"(m)
+                 : "v"(below), "v"(above));
+}
+
 // The transform's three segment reductions at once: p the inclusive prefix
 // minimum, q the inclusive suffix minimum, m the segment minimum.
 template <int SEG>

@@ -129,7 +129,7 @@ enum { PAIR_SRC_OWN = 0, PAIR_SRC_PARENT = 1, PAIR_SRC_ZERO = 2 };
 bp_status launch_iteration_pair(const Plan &p, int l, int src_kind, size_t src_off, size_t dst_off, bool write_c1,
                                 float lambda, float tau, int32_t *disp, uint8_t *ws, hipStream_t s,
                                 uint8_t *ck = nullptr, bool ck_c1 = false, float *soft = nullptr,
-                                float inv_t = 0.0f);
+                                float inv_t = 0.0f, int pairs = 1);
 
 // Half-sweep t of the finest level reading its incoming messages from `src`
 // (a saved state in the level's layout) and writing the receivers' slots
@@ -259,7 +259,8 @@ struct PairArgs {
     float lambda, lt;
     int near;              // window of the transform's near form: 1 (tau <= 2), 2 (tau <= 3), 0 (scans)
     int cost_fmt;          // the level's cost storage (COST_*; selects the kernel)
-    int tx, ty;            // tile (tx even)
+    int pairs;             // pairs of half-sweeps per launch: 1 tiled, more streamed
+    int tx, ty;            // tile (tx even), or the strips' columns and the segments' rows
     int tiles_x, ntiles, per_xcd;
     uint8_t *ck;           // checkpoint state in the level's layout that also receives phase 2's rows,
                            // or NULL
@@ -273,7 +274,23 @@ bp_status dispatch_iter_pm2(const PairArgs &a, int fmt, int S, int R, bool ro, h
 bool pair_supported(int S, int R);
 PairArgs make_pair_args(const Plan &p, int l, int src_kind, size_t src_off, size_t dst_off, bool write_c1,
                         float lambda, float tau, int32_t *disp, uint8_t *ws, uint8_t *ck = nullptr,
-                        bool ck_c1 = false, float *soft = nullptr, float inv_t = 0.0f);
+                        bool ck_c1 = false, float *soft = nullptr, float inv_t = 0.0f, int pairs = 1);
+// Several pairs of half-sweeps in one launch (bp_iter_stream_impl.h).
+// PairSchedule: the launches that run a level's pairs, `ones` of one pair
+// (tiled), then `threes` of three and `twos` of two.  pair_schedule decides it
+// for level l's `np` pairs; one pair each when the launches also save states
+// for the adjoint; with even_count the number of launches is even unless np
+// is odd and all are single.
+struct PairSchedule {
+    int ones, threes, twos;
+    int count() const { return ones + threes + twos; }
+    int pairs(int i) const { return i < ones ? 1 : i < ones + threes ? 3 : 2; }   // of launch i
+};
+PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, bool even_count);
+void stream_shape(PairArgs *a, int S, int R);
+bp_status dispatch_iter_stream(const PairArgs &a, int fmt, int S, int R, hipStream_t s);
+// Window of the transform's near form: 1 (tau <= 2), 2 (tau <= 3), 0 (scans).
+inline int near_window(float tau) { return tau <= 2.0f ? 1 : tau <= 3.0f ? 2 : 0; }
 // Zero the out-of-grid slots of `n` message states of each of `count`
 // problems: problem i's states are laid out like level 0 of plans[i], back to
 // back from bases[i] (checkpoint states written by the fused pairs, which

@@ -1,0 +1,143 @@
+// a5, pixel-major levels: host side of the streamed half-sweeps (the kernel is
+// in bp_iter_stream_impl.h, compiled per message storage format in
+// bp_iter_stream_f32.hip, _f16.hip and _bf16.hip): which levels use them, the
+// strips and segments of a launch, and dispatch by storage format.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "bp_device.h"
+#include "bp_internal.h"
+#include "bp_iter_stream.h"
+
+namespace bpk {
+
+constexpr int kSlots = 256;   // blocks resident at a time: one per compute unit
+
+// Strips of a w-wide level for blocks of `nc` columns that run T half-sweeps:
+// tx columns with T - 1 more on each side (none beyond the grid), as wide as
+// the block allows.
+static int strip_width(int w, int nc, int T)
+{
+    const int H = T - 1;
+    for (int n = 1;; ++n) {
+        const int t = (w + n - 1) / n;
+        if ((n == 1 ? t : n == 2 ? t + H : t + 2 * H) <= nc) return t;
+    }
+}
+
+// Rows of a segment: the count of segments with the least time in the model
+//   rounds of resident blocks x steps of a block,
+// where a block of t rows takes t + 3 (T - 1) steps: short segments repeat the
+// T - 1 rows at their ends and fill the pipeline of stages anew, long ones
+// leave compute units idle.
+static int segment_rows(int h, int strips, int T)
+{
+    const int H = T - 1, most = std::max(1, std::min(h, 4 * kSlots / strips));
+    int64_t best = -1;
+    int ty = h;
+    for (int k = 1; k <= most; ++k) {
+        const int t = (h + k - 1) / k;
+        const int64_t blocks = (int64_t)strips * ((h + t - 1) / t);
+        const int64_t cost = (blocks + kSlots - 1) / kSlots * (t + 3 * H);
+        if (best < 0 || cost < best) {
+            best = cost;
+            ty = t;
+        }
+    }
+    return ty;
+}
+
+// Pairs of half-sweeps per launch for a level (1: the tiled pair).  Streaming
+// needs enough pixels to fill the chip with strips of rows: a step of a block
+// takes about 0.7 us however few blocks there are, and every segment repeats
+// rows and fills its pipeline.  Measured per pair, tiled / two / three pairs
+// per launch, FP32 rows, tau 2 (w x h x labels):
+//   240 x 135 x 64   (2.1 M values)  10.4 / 11.8 / 12.5 us
+//   338 x 190 x 64   (4.1 M)         16.9 / 14.3 / 15.3
+//   676 x 380 x 16   (4.1 M)         17.8 / 14.3 / 15.1
+//   676 x 380 x 32   (8.2 M)         27.5 / 20.4 / 21.1
+//   676 x 380 x 64   (16.4 M)        60.6 / 33.1 / 31.3
+//   1352 x 760 x 64  (65.8 M)         244 /  121 /  95
+//   480 x 270 x 96   (12.4 M)        41.8 / 27.6 / 27.8
+//   676 x 380 x 96   (24.7 M)         101 /   56 /  50
+//   1352 x 760 x 128 (132 M)          488 /  258 / (434, spilling)
+// with FP16 rows
+//   240 x 135 x 128  (4.1 M)         15.4 / 16.8
+//   338 x 190 x 64   (4.1 M)         17.5 / 16.0 / 16.6
+//   676 x 380 x 64                   46.4 / 39.1 / 36.1
+//   480 x 270 x 128  (16.6 M)        44.4 / 38.9 / 43.0
+//   1352 x 760 x 128                  384 /  277 /  249
+// so for tau <= 2 two pairs from 4 M values (6 M for 16-bit rows of more than
+// four labels per lane) and three from 16 M (24 M).  The five-label form (tau
+// 2.6: 480 x 270 x 32 17.7 / 19.0, 676 x 380 x 32 30.2 / 25.2 us) needs 8 M and
+// stops at two pairs, where three spill or wait more (1352 x 760 x 128 in
+// bfloat16: 438 / 291 / 378 us), the scans (tau 5: 676 x 380 x 32 33.0 / 33.1,
+// 676 x 380 x 64 65.6 / 48; FP16 676 x 380 x 96 83 / 86) 12 M, and 32 M with
+// 16-bit rows: the more instructions a message takes, the less the memory
+// traffic that streaming saves was what held the tiled pair back.
+static int stream_pairs(const Level &v, int L, int near)
+{
+    int S, R;
+    pm_split(L, &S, &R);
+    const int nc = stream_columns(S, R);
+    if (L != S * R || nc == 0 || v.layout != PIXEL_MAJOR) return 1;
+    if (v.cost_fmt == COST_F16 && R % 4 == 0) return 1;   // those lanes hold byte costs
+    const int64_t n = (int64_t)v.w * v.h * v.lp;
+    const bool f32 = v.fmt == FMT_F32;
+    const int64_t two = near == 1 ? (f32 || R <= 4 ? 4000000 : 6000000) : near == 2 ? 8000000 : f32 ? 12000000 : 32000000;
+    if (v.w < 2 * nc || v.h < 64 || n < two) return 1;
+    return near == 1 && stream_three(R, v.fmt) && n >= (R <= 4 ? 16000000 : 24000000) ? 3 : 2;
+}
+
+PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, bool even_count)
+{
+    const int most = saves ? 1 : stream_pairs(p.lv[l], p.L, near_window(tau));
+    PairSchedule s{0, 0, 0};
+    if (most == 3 && np >= 2) {
+        // As few launches as possible.
+        const int launches = (np + 2) / 3;
+        s.threes = np - 2 * launches;
+        s.twos = launches - s.threes;
+    } else if (most >= 2) {
+        // A single pair comes first, where the incoming state is the parent
+        // level's (a quarter of the rows to read) or zero.
+        s.ones = np & 1;
+        s.twos = np / 2;
+    } else {
+        s.ones = np;
+    }
+    if (even_count && (s.count() & 1)) {
+        // One more launch: three pairs as one and two, or two as single ones.
+        if (s.threes > 0) {
+            --s.threes;
+            ++s.twos;
+            ++s.ones;
+        } else if (s.twos > 0) {
+            --s.twos;
+            s.ones += 2;
+        }
+    }
+    return s;
+}
+
+void stream_shape(PairArgs *a, int SEGV, int R)
+{
+    const int T = 2 * a->pairs;
+    a->tx = strip_width(a->w, stream_columns(SEGV, R), T);
+    a->tiles_x = (a->w + a->tx - 1) / a->tx;
+    a->ty = segment_rows(a->h, a->tiles_x, T);
+    a->ntiles = a->tiles_x * ((a->h + a->ty - 1) / a->ty);
+    a->per_xcd = (a->ntiles + 7) / 8;
+}
+
+bp_status dispatch_iter_stream(const PairArgs &a, int fmt, int SEGV, int R, hipStream_t st)
+{
+    switch (fmt) {
+    case FMT_F16: return stream_launch<StoreF16>(a, SEGV, R, st);
+    case FMT_BF16: return stream_launch<StoreBF16>(a, SEGV, R, st);
+    default: return stream_launch<StoreF32>(a, SEGV, R, st);
+    }
+}
+
+}  // namespace bpk
