@@ -20,6 +20,15 @@
 // with winner g in increasing f.  An untruncated winner lies within tau of f
 // (h(g) + lambda |f - g| <= min h + lambda tau), so f only ranges over a
 // window of `win` labels around g (all labels when lambda = 0).
+//
+// A window of at most kNear labels (tau < 3) reaches no further than the next
+// lane.  Then the scans need only that lane's values (what comes from further
+// off exceeds min h + lambda tau whatever it is, and so does everything that
+// depends on it), and phase 2 takes the next lanes' posts through DPP: no LDS,
+// and the adds of a label in the same order.  At eight 320 x 240 x 64 problems
+// (1.18 GB moved per reverse step) the general form issues about 2460 VALU
+// instructions per wavefront and runs 239 us, issue bound; the near one 1480
+// and 210 us, 5.6 TB/s: memory bound.
 #include <hip/hip_runtime.h>
 
 #include "bp_device.h"
@@ -144,7 +153,13 @@ __device__ __forceinline__ void pair_suffix_excl(float v, int vi, int s, float &
     }
 }
 
-template <int SEG, int R>
+// Window, in labels, of the near form (kNear <= R).
+constexpr int kNear = 4;
+
+// Byte offset past every row: loads there return zero, stores are dropped.
+constexpr uint32_t kNoRow = 0xffffff00u;
+
+template <int SEG, int R, bool NEAR>
 __device__ __forceinline__ void bwd_step_pm(const BwdPmArgs &a, uint32_t block)
 {
     // The forward arithmetic is repeated exactly as the half-sweep kernels
@@ -158,30 +173,27 @@ __device__ __forceinline__ void bwd_step_pm(const BwdPmArgs &a, uint32_t block)
     // of up to PAD labels around a lane's labels needs no clamping at the
     // row's ends.
     static_assert(LP <= kMaxBackwardLabels && kMaxBackwardLabels <= 128, "winners must fit a signed byte");
+    static_assert(kNear <= R, "the near form reaches one lane");
     constexpr int PAD = 4;
     constexpr int PROW = 4 * (LP + PAD) + PAD;
-    __shared__ float s_pv[PPB * PROW];
-    __shared__ int8_t s_pw[PPB * PROW];
+    __shared__ float s_pv[NEAR ? 1 : PPB * PROW];
+    __shared__ int8_t s_pw[NEAR ? 1 : PPB * PROW];
     __shared__ float s_part[4][2];
     const uint32_t gid = block * 256u + threadIdx.x;
     const int j = (int)(gid / SEG);
     const int s = (int)(gid % SEG);
     const int f0 = s * R;
     const int prow = (int)(threadIdx.x / SEG) * PROW;
-    for (int e = (int)threadIdx.x; e < PPB * 5 * PAD; e += 256) {
-        const int px = e / (5 * PAD), q = e - px * (5 * PAD);
-        const int at = px * PROW + (q / PAD) * (LP + PAD) + q % PAD;
-        s_pv[at] = 0.0f;
-        s_pw[at] = -1;
+    if constexpr (!NEAR) {
+        for (int e = (int)threadIdx.x; e < PPB * 5 * PAD; e += 256) {
+            const int px = e / (5 * PAD), q = e - px * (5 * PAD);
+            const int at = px * PROW + (q / PAD) * (LP + PAD) + q % PAD;
+            s_pv[at] = 0.0f;
+            s_pw[at] = -1;
+        }
     }
-    bool live = j < a.ncomp;
-    int y = 0, x = 0;
-    if (live) {
-        y = j / a.wh;
-        x = 2 * (j - y * a.wh) + ((y + a.colour) & 1);
-        live = x < a.w;
-    }
-    const uint32_t jj = live ? (uint32_t)j : 0u;
+    const int y = j / a.wh, x = 2 * (j - y * a.wh) + ((y + a.colour) & 1);
+    const bool live = j < a.ncomp && x < a.w;
     const bool has[4] = {live && x > 0, live && x < a.w - 1, live && y > 0, live && y < a.h - 1};
     const __amdgpu_buffer_rsrc_t rc = make_rsrc(a.cost, a.cost_bytes);
     const __amdgpu_buffer_rsrc_t rm = make_rsrc(a.msg, a.msg_bytes);
@@ -190,41 +202,36 @@ __device__ __forceinline__ void bwd_step_pm(const BwdPmArgs &a, uint32_t block)
     const float inf = __builtin_huge_valf();
     const float lam = a.lambda;
     const float lamR = lam * (float)R;
-    const uint32_t base = jj * a.lp + (uint32_t)f0;
+    const uint32_t base = (uint32_t)j * a.lp + (uint32_t)f0;
+    const uint32_t cb = (uint32_t)a.colour * a.blk, mb4 = 4u * cb;   // the colour's blocks of cost and messages
 
     // The four receiver slots' adjoints (zeros for a missing neighbour), the
     // cost adjoint this pixel accumulates, the cost and the four incoming
-    // rows, all loaded before any arithmetic.  The receiver slots are not
-    // cleared: every in-grid slot of the receivers' colour is overwritten by
-    // the next reverse step's sender side before anything reads it again.
+    // rows, all loaded before any arithmetic.  At the first reverse step a
+    // slot's adjoint is its pixel's readout adjoint, which the cost adjoint
+    // holds.  The receiver slots are not cleared: every in-grid slot of the
+    // receivers' colour is overwritten by the next reverse step's sender side
+    // before anything reads it again.
     float mbv[4][R];
+    const uint32_t other = a.blk - cb;                      // the other colour's block (colour 0 or 1)
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        uint32_t roff = 0;
-        if (has[k]) {
-            int nx = x, ny = y;
-            if (k == 0) nx = x - 1;
-            else if (k == 1) nx = x + 1;
-            else if (k == 2) ny = y - 1;
-            else ny = y + 1;
-            const uint32_t dj = (uint32_t)(ny * a.wh + (nx >> 1));
-            roff = (((uint32_t)(a.colour ^ 1) * 4u + (uint32_t)(k ^ 1)) * a.blk + dj * a.lp + (uint32_t)f0) * 4u;
-        }
-        ld_row<StoreF32, R>(rb, roff, mbv[k]);
-#pragma unroll
-        for (int r = 0; r < R; ++r) mbv[k][r] = has[k] ? mbv[k][r] : 0.0f;
+        const int nx = k == 0 ? x - 1 : k == 1 ? x + 1 : x, ny = k == 2 ? y - 1 : k == 3 ? y + 1 : y;
+        const uint32_t row = (uint32_t)(ny * a.wh + (nx >> 1)) * a.lp + (uint32_t)f0;
+        const uint32_t slot = a.first ? other : 4u * other + (uint32_t)(k ^ 1) * a.blk;
+        ld_row<StoreF32, R>(a.first ? rg : rb, has[k] ? (slot + row) * 4u : kNoRow, mbv[k]);
     }
-    const uint32_t goff = ((uint32_t)a.colour * a.blk + base) * 4u;
+    const uint32_t goff = live ? (cb + base) * 4u : kNoRow;
     float gc[R];
-    if (live) ld_row<StoreF32, R>(rg, goff, gc);
+    ld_row<StoreF32, R>(rg, goff, gc);
     // h of the four outgoing messages, summed as in the forward kernels.
     float h[4][R];
     {
         float c[R], m[4][R];
-        ld_row<StoreF32, R>(rc, ((uint32_t)a.colour * a.blk + base) * 4u, c);
+        ld_row<StoreF32, R>(rc, goff, c);
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
-            ld_row<StoreF32, R>(rm, (((uint32_t)a.colour * 4u + (uint32_t)kk) * a.blk + base) * 4u, m[kk]);
+            ld_row<StoreF32, R>(rm, live ? (mb4 + (uint32_t)kk * a.blk + base) * 4u : kNoRow, m[kk]);
         pm_h4<R>(c, m, h);
 #pragma unroll
         for (int k = 0; k < 4; ++k)
@@ -233,52 +240,55 @@ __device__ __forceinline__ void bwd_step_pm(const BwdPmArgs &a, uint32_t block)
                 if (f0 + r >= a.L) h[k][r] = inf;
     }
 
-    // Phase 1, message by message: the transform with winners, then post
+    // Phase 1, message by message: the transform with winners (label minus f0,
+    // as floats: exact, and |f - winner| needs no conversion), then post
     // (winner, mb) of the receiver slot's adjoint.
-    float lsum = 0.0f, tsum = 0.0f, nsum[4];
-    int gmin[4];
+    float lsum = 0.0f, tsum = 0.0f, nsum[4], hb[4][R];
+    float gmin[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         // Lowest minimiser of h.
-        float hmin = inf;
-        int gm = 0;
+        float hmin = h[k][0];
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (h[k][r] < hmin) {
-                hmin = h[k][r];
-                gm = f0 + r;
-            }
-        seg_argmin<SEG>(hmin, gm);
-        gmin[k] = gm;
+        for (int r = 1; r < R; ++r) hmin = fminf(hmin, h[k][r]);
+        hmin = seg_allmin<SEG>(hmin);
+        float gm = (float)LP;
+#pragma unroll
+        for (int r = R - 1; r >= 0; --r) gm = h[k][r] == hmin ? (float)(f0 + r) : gm;
+        gmin[k] = seg_allmin<SEG>(gm) - (float)f0;
         // Forward pass with winners.
-        float A[R];
-        int wa[R];
+        float A[R], wa[R];
         A[0] = h[k][0];
-        wa[0] = f0;
+        wa[0] = 0.0f;
 #pragma unroll
         for (int r = 1; r < R; ++r) {
             const float v = A[r - 1] + lam;
             const bool keep = h[k][r] <= v;
             A[r] = keep ? h[k][r] : v;
-            wa[r] = keep ? f0 + r : wa[r - 1];
+            wa[r] = keep ? (float)r : wa[r - 1];
         }
         {
-            float pv;
-            int pi;
-            pair_prefix_excl<SEG>(A[R - 1] - lamR * (float)s, wa[R - 1], s, pv, pi);
+            float pv, pi;
+            const float u = A[R - 1] - lamR * (float)s;
+            if constexpr (NEAR) {
+                pv = seg_from_lower<SEG, 1>(u, inf, s);
+                pi = seg_from_lower<SEG, 1>(wa[R - 1], 0.0f, s) - (float)R;
+            } else {
+                int i;
+                pair_prefix_excl<SEG>(u, f0 + (int)wa[R - 1], s, pv, i);
+                pi = (float)(i - f0);
+            }
             const float carry = pv + lamR * (float)(s - 1);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const float cand = carry + lam * (float)(r + 1);
-                if (cand < A[r]) {
-                    A[r] = cand;
-                    wa[r] = pi;
-                }
+                const bool take = cand < A[r];
+                A[r] = take ? cand : A[r];
+                wa[r] = take ? pi : wa[r];
             }
         }
         // Backward pass with winners.
-        float B[R];
-        int wb[R];
+        float B[R], wb[R];
         B[R - 1] = A[R - 1];
         wb[R - 1] = wa[R - 1];
 #pragma unroll
@@ -289,78 +299,105 @@ __device__ __forceinline__ void bwd_step_pm(const BwdPmArgs &a, uint32_t block)
             wb[r] = take ? wb[r + 1] : wa[r];
         }
         {
-            float qv;
-            int qi;
-            pair_suffix_excl<SEG>(B[0] + lamR * (float)s, wb[0], s, qv, qi);
+            float qv, qi;
+            const float u = B[0] + lamR * (float)s;
+            if constexpr (NEAR) {
+                qv = seg_from_upper<SEG, 1>(u, inf, s);
+                qi = seg_from_upper<SEG, 1>(wb[0], 0.0f, s) + (float)R;
+            } else {
+                int i;
+                pair_suffix_excl<SEG>(u, f0 + (int)wb[0], s, qv, i);
+                qi = (float)(i - f0);
+            }
             const float carry = qv - lamR * (float)(s + 1);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const float cand = carry + lam * (float)(R - r);
-                if (cand < B[r]) {
-                    B[r] = cand;
-                    wb[r] = qi;
-                }
+                const bool take = cand < B[r];
+                B[r] = take ? cand : B[r];
+                wb[r] = take ? qi : wb[r];
             }
         }
         const float cap = hmin + a.lt;
-        float ns = 0.0f;
+        float ns = 0.0f, post[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int f = f0 + r;
-            const float mb = f < a.L ? mbv[k][r] : 0.0f;
-            int src = -1;
-            float post = 0.0f;
-            if (cap < B[r]) {
-                lsum += mb * a.tau;
-                tsum += mb * a.lambda;
-            } else {
-                src = wb[r];
-                post = mb;
-                ns += mb;
-                lsum += mb * fabsf((float)(f - src));
-            }
-            s_pv[prow + PAD + k * (LP + PAD) + f] = post;
-            s_pw[prow + PAD + k * (LP + PAD) + f] = (int8_t)src;
+            const float mb = f0 + r < a.L ? mbv[k][r] : 0.0f;
+            const bool cut = cap < B[r];
+            post[r] = cut ? 0.0f : mb;
+            ns += post[r];
+            lsum += mb * (cut ? a.tau : fabsf((float)r - wb[r]));
+            tsum += cut ? mb * a.lambda : 0.0f;
+            wb[r] = cut ? 1024.0f : wb[r];                  // no label
         }
         nsum[k] = ns;
+        if constexpr (NEAR) {
+            // Phase 2: h-bar of this lane's labels from the posts within kNear
+            // labels of them, in increasing label.
+#pragma unroll
+            for (int r = 0; r < R; ++r) hb[k][r] = 0.0f;
+#pragma unroll
+            for (int i = R - kNear; i < R; ++i) {
+                const float pv = seg_from_lower<SEG, 1>(post[i], 0.0f, s), w = seg_from_lower<SEG, 1>(wb[i], 0.0f, s);
+#pragma unroll
+                for (int r = 0; r <= i - (R - kNear); ++r) hb[k][r] += w == (float)(R + r) ? pv : 0.0f;
+            }
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (i - r <= kNear && r - i <= kNear) hb[k][r] += wb[i] == (float)r ? post[i] : 0.0f;
+#pragma unroll
+            for (int i = 0; i < kNear; ++i) {
+                const float pv = seg_from_upper<SEG, 1>(post[i], 0.0f, s), w = seg_from_upper<SEG, 1>(wb[i], 0.0f, s);
+#pragma unroll
+                for (int r = R - kNear + i; r < R; ++r) hb[k][r] += w == (float)(r - R) ? pv : 0.0f;
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                s_pv[prow + PAD + k * (LP + PAD) + f0 + r] = post[r];
+                s_pw[prow + PAD + k * (LP + PAD) + f0 + r] = wb[r] < 1024.0f ? (int8_t)(f0 + (int)wb[r]) : (int8_t)-1;
+            }
+        }
     }
-    __syncthreads();
 
     // Phase 2: h-bar of this lane's labels for each message.  One pass over
     // the posts that can reach them (winners lie within `win` of their
     // label); every h-bar(g) still adds its posts in increasing f.
-    float hb[4][R];
+    if constexpr (!NEAR) __syncthreads();
     const int lo = f0 - a.win > 0 ? f0 - a.win : 0;
     const int hi = f0 + R - 1 + a.win < LP - 1 ? f0 + R - 1 + a.win : LP - 1;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const float ntot = seg_allreduce<SEG>(nsum[k], [](float p, float q) { return p + q; });
+        if constexpr (!NEAR) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) hb[k][r] = 0.0f;
-        const int row = prow + PAD + k * (LP + PAD);
-        if (a.win <= PAD) {
-            // Every lane the same count of posts, the pads past the row's
-            // ends included (they match no label).
-            const int n = R + 2 * a.win, p0 = row + f0 - a.win;
-            for (int i = 0; i < n; ++i) {
-                const float pv = s_pv[p0 + i];
-                const int wv = s_pw[p0 + i];
+            for (int r = 0; r < R; ++r) hb[k][r] = 0.0f;
+            const int row = prow + PAD + k * (LP + PAD);
+            if (a.win <= PAD) {
+                // Every lane the same count of posts, the pads past the row's
+                // ends included (they match no label).
+                const int n = R + 2 * a.win, p0 = row + f0 - a.win;
+                for (int i = 0; i < n; ++i) {
+                    const float pv = s_pv[p0 + i];
+                    const int wv = s_pw[p0 + i];
 #pragma unroll
-                for (int r = 0; r < R; ++r)
-                    if (wv == f0 + r) hb[k][r] += pv;
-            }
-        } else {
-            for (int f = lo; f <= hi; ++f) {
-                const float pv = s_pv[row + f];
-                const int d = (int)s_pw[row + f] - f0;
+                    for (int r = 0; r < R; ++r)
+                        if (wv == f0 + r) hb[k][r] += pv;
+                }
+            } else {
+                for (int f = lo; f <= hi; ++f) {
+                    const float pv = s_pv[row + f];
+                    const int d = (int)s_pw[row + f] - f0;
 #pragma unroll
-                for (int r = 0; r < R; ++r)
-                    if (d == r) hb[k][r] += pv;
+                    for (int r = 0; r < R; ++r)
+                        if (d == r) hb[k][r] += pv;
+                }
             }
         }
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (f0 + r == gmin[k]) hb[k][r] -= ntot;
+        for (int r = 0; r < R; ++r) hb[k][r] -= gmin[k] == (float)r ? ntot : 0.0f;
     }
 
     // Sender side: cost-bar += sum over messages; slot k's adjoint gets the
@@ -369,26 +406,20 @@ __device__ __forceinline__ void bwd_step_pm(const BwdPmArgs &a, uint32_t block)
     float tot[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) tot[r] = (hb[0][r] + hb[1][r]) + (hb[2][r] + hb[3][r]);
-    if (live) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) gc[r] += tot[r];
-        st_row<StoreF32, R>(rg, goff, gc);
-    }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        if (!has[k]) continue;
-        const uint32_t moff = (((uint32_t)a.colour * 4u + (uint32_t)k) * a.blk + base) * 4u;
         float cur[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) cur[r] = tot[r] - hb[k][r];
         if (a.first) {
-            ld_row<StoreF32, R>(rb, moff, cur);
 #pragma unroll
-            for (int r = 0; r < R; ++r) cur[r] += tot[r] - hb[k][r];
-        } else {
-#pragma unroll
-            for (int r = 0; r < R; ++r) cur[r] = tot[r] - hb[k][r];
+            for (int r = 0; r < R; ++r) cur[r] += gc[r];
         }
-        st_row<StoreF32, R>(rb, moff, cur);
+        st_row<StoreF32, R>(rb, has[k] ? (mb4 + (uint32_t)k * a.blk + base) * 4u : kNoRow, cur);
     }
+#pragma unroll
+    for (int r = 0; r < R; ++r) gc[r] += tot[r];
+    st_row<StoreF32, R>(rg, goff, gc);
 
     // Block sums of the lambda and tau partials: per wavefront by shuffles,
     // then the four wavefronts in order.
@@ -419,35 +450,28 @@ struct BwdPmChunk {
     int n;
 };
 
-__global__ void k_write_bwd_pm_entries(BwdPmEntry *__restrict__ dst, BwdPmChunk c)
-{
-    const int i = threadIdx.x;
-    if (i < c.n) dst[i] = c.e[i];
-}
-
 // The reverse half-sweep of several problems (same lane split) in one
-// launch: block b belongs to the last entry whose first block is <= b.
-template <int SEG, int R>
-__global__ void __launch_bounds__(256) k_bwd_step_pm_batch(const BwdPmEntry *__restrict__ tab, int n)
+// launch, their arguments passed by value: block b belongs to the last entry
+// whose first block is <= b.
+template <int SEG, int R, bool NEAR>
+__global__ void __launch_bounds__(256) k_bwd_step_pm_batch(const BwdPmChunk c)
 {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (tab[mid].block0 <= (int)blockIdx.x) lo = mid;
-        else hi = mid - 1;
-    }
-    bwd_step_pm<SEG, R>(tab[lo].a, blockIdx.x - (uint32_t)tab[lo].block0);
+    int i = 0;
+    while (i + 1 < c.n && c.e[i + 1].block0 <= (int)blockIdx.x) ++i;
+    bwd_step_pm<SEG, R, NEAR>(c.e[i].a, blockIdx.x - (uint32_t)c.e[i].block0);
 }
 
 // Readout adjoint on pixel-major states: b = cost + the four incoming rows
 // (summed as the forward readout sums them), d = sum f p_f with p =
 // softmax(-b / T); b-bar(f) = -(g / T) p_f (f - d).  Initialises the cost
-// adjoint and every in-grid incoming slot of the message adjoint.  Grid
+// adjoint; every incoming slot's adjoint is its pixel's b-bar too, and the
+// first reverse step reads it there (writing the eight slot rows per pixel
+// pair as well: 34 against 23 us at 320 x 240 x 64).  Memory bound.  Grid
 // (ncomp * SEG / 256, 2 colours).
 template <int SEG, int R>
 __global__ void __launch_bounds__(256) k_bwd_readout_pm(const float *__restrict__ cost, uint32_t cost_bytes,
                                                        const uint8_t *__restrict__ msg, uint32_t msg_bytes,
-                                                       float *__restrict__ mbar, float *__restrict__ gcost,
+                                                       float *__restrict__ gcost,
                                                        const float *__restrict__ grad_soft, PmDesc d, int L,
                                                        float inv_t)
 {
@@ -460,7 +484,6 @@ __global__ void __launch_bounds__(256) k_bwd_readout_pm(const float *__restrict_
     if (x >= d.w) return;
     const __amdgpu_buffer_rsrc_t rc = make_rsrc(cost, cost_bytes);
     const __amdgpu_buffer_rsrc_t rm = make_rsrc(msg, msg_bytes);
-    const __amdgpu_buffer_rsrc_t rb = make_rsrc(mbar, msg_bytes);
     const __amdgpu_buffer_rsrc_t rg = make_rsrc(gcost, cost_bytes);
     const int f0 = s * R;
     const uint32_t lp = (uint32_t)d.lp, blk = (uint32_t)d.blk;
@@ -494,10 +517,6 @@ __global__ void __launch_bounds__(256) k_bwd_readout_pm(const float *__restrict_
 #pragma unroll
     for (int r = 0; r < R; ++r) bb[r] = f0 + r < L ? -g * inv_t * (wgt[r] / den) * ((float)(f0 + r) - dd) : 0.0f;
     st_row<StoreF32, R>(rg, ((uint32_t)c * blk + base) * 4u, bb);
-    const bool has[4] = {x > 0, x < d.w - 1, y > 0, y < d.h - 1};
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if (has[k]) st_row<StoreF32, R>(rb, (((uint32_t)c * 4u + (uint32_t)k) * blk + base) * 4u, bb);
 }
 
 // Pixel-major cost adjoint -> planar [L][h][w] output, through an LDS tile
@@ -570,8 +589,8 @@ int bwd_pm_blocks(const Plan &p)
     return (int)(((int64_t)p.lv[0].h * p.lv[0].wh * S + 255) / 256);
 }
 
-bp_status launch_bwd_readout_pm(const Plan &p, const uint8_t *msg, float *mbar, float *gcost, const float *grad_soft,
-                                float temperature, uint8_t *ws, hipStream_t s)
+bp_status launch_bwd_readout_pm(const Plan &p, const uint8_t *msg, float *gcost, const float *grad_soft, float temperature,
+                                uint8_t *ws, hipStream_t s)
 {
     const Level &v = p.lv[0];
     const int64_t ncomp = (int64_t)v.h * v.wh;
@@ -582,7 +601,7 @@ bp_status launch_bwd_readout_pm(const Plan &p, const uint8_t *msg, float *mbar, 
 #define BP_RPM(SV, RV)                                                                                             \
     if (S == SV && R == RV) {                                                                                      \
         k_bwd_readout_pm<SV, RV><<<dim3((unsigned)((ncomp * SV + 255) / 256), 2), 256, 0, s>>>(                    \
-            cost, (uint32_t)v.cost_bytes, msg, (uint32_t)v.msg_bytes, mbar, gcost, grad_soft, pm_desc(v), p.L, inv_t); \
+            cost, (uint32_t)v.cost_bytes, msg, (uint32_t)v.msg_bytes, gcost, grad_soft, pm_desc(v), p.L, inv_t); \
         return launch_status();                                                                                    \
     }
     BP_RPM(4, 4) BP_RPM(8, 4) BP_RPM(16, 4) BP_RPM(16, 6) BP_RPM(16, 8)
@@ -610,31 +629,32 @@ bp_status launch_gcost_to_planar(const Plan &p, const float *gcost, float *grad_
     return launch_status();
 }
 
-size_t bwd_pm_table_bytes(int count) { return align_up((size_t)count * sizeof(BwdPmEntry)); }
+// The near form's condition: untruncated winners within kNear labels.
+static bool bwd_near(float lambda, int win) { return lambda > 0.0f && win <= kNear; }
 
 bp_status launch_bwd_step_pm_batch(const BwdPmProblem *probs, int count, int t, bool first_step, float lambda,
-                                   float tau, uint8_t *table, hipStream_t s)
+                                   float tau, hipStream_t s)
 {
-    BwdPmEntry *dev = (BwdPmEntry *)table;
     bool *done = new bool[count]();
-    BwdPmEntry *host = new BwdPmEntry[count];
     bp_status st = BP_OK;
-    int used = 0;
-    // One launch per lane split (the kernel's template arguments).
+    // Launches of up to kBwdPmChunk problems of one lane split (the kernel's
+    // template arguments) and window.
     for (int i = 0; i < count && st == BP_OK; ++i) {
         if (done[i]) continue;
         int S, R;
         pm_split(probs[i].plan->L, &S, &R);
-        const int first = used;
+        bool near = false;
         int blocks = 0;
-        for (int k = i; k < count; ++k) {
+        BwdPmChunk c;
+        c.n = 0;
+        for (int k = i; k < count && c.n < kBwdPmChunk; ++k) {
             int Sk, Rk;
             pm_split(probs[k].plan->L, &Sk, &Rk);
             if (done[k] || Sk != S || Rk != R) continue;
             done[k] = true;
             const Plan &p = *probs[k].plan;
             const Level &v = p.lv[0];
-            BwdPmEntry &e = host[used++];
+            BwdPmEntry &e = c.e[c.n++];
             BwdPmArgs &a = e.a;
             a.cost = (const float *)(probs[k].ws + v.cost_off);
             a.cost_bytes = (uint32_t)v.cost_bytes;
@@ -655,6 +675,7 @@ bp_status launch_bwd_step_pm_batch(const BwdPmProblem *probs, int count, int t, 
             // Untruncated winners lie within tau of their label; two labels of
             // margin cover rounding.  Without smoothness any label can win.
             a.win = lambda > 0.0f ? (int)std::min((float)(v.lp - 1), std::floor(tau) + 2.0f) : v.lp - 1;
+            near = bwd_near(lambda, a.win);               // the same for a lane split
             a.first = first_step ? 1 : 0;
             a.lambda = lambda;
             a.tau = tau;
@@ -662,19 +683,10 @@ bp_status launch_bwd_step_pm_batch(const BwdPmProblem *probs, int count, int t, 
             e.block0 = blocks;
             blocks += bwd_pm_blocks(p);
         }
-        for (int c0 = first; c0 < used && st == BP_OK; c0 += kBwdPmChunk) {
-            BwdPmChunk c;
-            c.n = used - c0 < kBwdPmChunk ? used - c0 : kBwdPmChunk;
-            for (int k = 0; k < c.n; ++k) c.e[k] = host[c0 + k];
-            k_write_bwd_pm_entries<<<1, 64, 0, s>>>(dev + c0, c);
-            st = launch_status();
-        }
-        if (st != BP_OK) break;
-        const int n = used - first;
-        const BwdPmEntry *tab = dev + first;
 #define BP_BPM(SV, RV)                                                                                             \
     if (S == SV && R == RV) {                                                                                      \
-        k_bwd_step_pm_batch<SV, RV><<<blocks, 256, 0, s>>>(tab, n);                                                \
+        if (near) k_bwd_step_pm_batch<SV, RV, true><<<blocks, 256, 0, s>>>(c);                                     \
+        else k_bwd_step_pm_batch<SV, RV, false><<<blocks, 256, 0, s>>>(c);                                         \
         st = launch_status();                                                                                      \
         continue;                                                                                                  \
     }
@@ -683,7 +695,6 @@ bp_status launch_bwd_step_pm_batch(const BwdPmProblem *probs, int count, int t, 
         st = BP_ERR_UNSUPPORTED;
     }
     delete[] done;
-    delete[] host;
     return st;
 }
 

@@ -1132,12 +1132,11 @@ bp_status bp_upsample_points(const int32_t *disp_lo, int32_t w_lo, int32_t h_lo,
                            R, disp_hi, camera, points, stream);
 }
 
-// Launch tables of the backward call: the reverse steps' entries, or the
-// batched rebuild half-sweeps' (one region, rewritten in stream order).
+// Launch tables of the backward call: the label-major reverse steps' entries,
+// or the batched rebuild half-sweeps' (one region, rewritten in stream order).
 static size_t bwd_tables_bytes(int32_t count)
 {
-    return std::max(std::max(bwd_table_bytes(count), bwd_pm_table_bytes(count)),
-                    align_up((size_t)count * sizeof(BatchEntry)));
+    return std::max(bwd_table_bytes(count), align_up((size_t)count * sizeof(BatchEntry)));
 }
 
 // One rebuild half-sweep r of every problem's finest level in one launch per
@@ -1283,7 +1282,8 @@ bp_status bp_backward(const bp_problem *probs, int32_t count, const bp_params *p
     const int nst = checkpoint_states(K, every);
     st = launch_zero(ws + zo, zb, stream);
     // Per problem: its checkpoints, state buffer, adjoints; the readout adjoint
-    // from the final state initialises the message adjoint and the cost adjoint.
+    // from the final state initialises the cost adjoint (and, label-major, the
+    // message adjoint).
     const uint8_t **ck = new const uint8_t *[count];
     BwdProblem *bp = new BwdProblem[count];
     BwdPmProblem *bq = new BwdPmProblem[count];
@@ -1308,7 +1308,7 @@ bp_status bp_backward(const bp_problem *probs, int32_t count, const bp_params *p
                 st = launch_bwd_readout(pl, last, mbar, grad_soft + soft_off, bp[i].grad_cost, params->temperature, ws,
                                         stream);
             else
-                st = launch_bwd_readout_pm(pl, last, mbar, bq[i].gcost, grad_soft + soft_off, params->temperature, ws,
+                st = launch_bwd_readout_pm(pl, last, bq[i].gcost, grad_soft + soft_off, params->temperature, ws,
                                            stream);
             soft_off += (size_t)probs[i].height * probs[i].width;
             cost_off += (size_t)probs[i].num_labels * probs[i].height * probs[i].width;
@@ -1363,7 +1363,7 @@ bp_status bp_backward(const bp_problem *probs, int32_t count, const bp_params *p
         }
         if (st != BP_OK) break;
         if (lm) st = launch_bwd_step_batch(bp, count, t, params->lambda, params->tau, ws + to, stream);
-        else st = launch_bwd_step_pm_batch(bq, count, t, t == K - 1, params->lambda, params->tau, ws + to, stream);
+        else st = launch_bwd_step_pm_batch(bq, count, t, t == K - 1, params->lambda, params->tau, stream);
     }
     if (!lm) {
         size_t cost_off = 0;

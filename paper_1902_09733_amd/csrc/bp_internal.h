@@ -218,11 +218,10 @@ struct BwdPmProblem {
     float *partial;         // bwd_pm_blocks(plan) (lambda, tau) pairs
 };
 int bwd_pm_blocks(const Plan &p);
-size_t bwd_pm_table_bytes(int count);
-bp_status launch_bwd_readout_pm(const Plan &p, const uint8_t *msg, float *mbar, float *gcost, const float *grad_soft,
-                                float temperature, uint8_t *ws, hipStream_t s);
+bp_status launch_bwd_readout_pm(const Plan &p, const uint8_t *msg, float *gcost, const float *grad_soft, float temperature,
+                                uint8_t *ws, hipStream_t s);
 bp_status launch_bwd_step_pm_batch(const BwdPmProblem *probs, int count, int t, bool first_step, float lambda,
-                                   float tau, uint8_t *table, hipStream_t s);
+                                   float tau, hipStream_t s);
 bp_status launch_gcost_to_planar(const Plan &p, const float *gcost, float *grad_cost, hipStream_t s);
 // Reverse half-sweep t of every problem, one launch per label count; the
 // launch entries are written into `table` (bwd_table_bytes(count) bytes).
