@@ -237,19 +237,20 @@ struct Recorder {
 };
 
 // Algorithmic memory traffic of one half-sweep and of one fused pair at
-// level l (bp_launch_record.bytes).
+// level l (bp_launch_record.bytes); a pair that reads out both colours stores
+// no state.
 double sweep_bytes(const Plan &pl, int l)
 {
     const double nl = (double)pl.lv[l].w * pl.lv[l].h * pl.L;
     return nl * (4.0 + 8.0 * fmt_bytes(pl.lv[l].fmt)) / 2.0;
 }
 
-double pair_bytes(const Plan &pl, int l, bool ends)
+double pair_bytes(const Plan &pl, int l, bool ends, bool reads_out)
 {
     const double nl = (double)pl.lv[l].w * pl.lv[l].h * pl.L, mb = fmt_bytes(pl.lv[l].fmt);
     const int cf = pl.lv[l].cost_fmt;
     const double cb = cf == COST_U8 ? 1.0 : cf == COST_F16 ? 2.0 : 4.0;   // both colours' costs
-    return nl * (cb + 4.0 * mb + (ends ? 2.0 * mb : 0.0));
+    return nl * (cb + (reads_out ? 2.0 : 4.0) * mb + (ends ? 2.0 * mb : 0.0));
 }
 
 // Runs the whole hierarchical BP of one problem.
@@ -269,6 +270,7 @@ bp_status run_one(const bp_problem &q, const Plan &pl, const bp_params &p, uint8
     // and their soft-argmin when it runs in a fused pair.
     const bool last_pair = level_pairs(pl, 0, K) && (K & 1) == 0;
     const bool fuse_ro = K >= 1 && (q.soft_disparity ? last_pair : q.disparity != nullptr);
+    bool ro_all = false;   // its last launch has read out both colours
     const float inv_t = q.soft_disparity ? 1.0f / p.temperature : 0.0f;
     for (int l = n - 1; l >= 0; --l) {
         int first_src = 0;
@@ -327,6 +329,7 @@ bp_status run_one(const bp_problem &q, const Plan &pl, const bp_params &p, uint8
                 // readout fused here and no export, nothing reads them (the
                 // final checkpoint receives them on its own).
                 const bool store_c1 = ends && (l > 0 || !rd || q.messages_out);
+                ro_all = rd && stream_reads_out(sched, q.messages_out, ckpt);
                 // State after the pair: saved (its colour-0 half) every
                 // `every` half-sweeps, and whole at the end.
                 uint8_t *ck = nullptr;
@@ -340,7 +343,7 @@ bp_status run_one(const bp_problem &q, const Plan &pl, const bp_params &p, uint8
                 if (rec && hipEventRecord(prof->ev[prof->n][0], s) != hipSuccess) return BP_ERR_HIP;
                 if ((st = launch_iteration_pair(pl, l, kind, src_off, dst_off, store_c1, p.lambda, p.tau,
                                                 rd ? q.disparity : nullptr, ws, s, ck, ends,
-                                                rd ? q.soft_disparity : nullptr, inv_t, sched.pairs(pi))) != BP_OK)
+                                                rd ? q.soft_disparity : nullptr, inv_t, sched.pairs(pi), ro_all)) != BP_OK)
                     return st;
                 if (rec) {
                     if (hipEventRecord(prof->ev[prof->n][1], s) != hipSuccess) return BP_ERR_HIP;
@@ -352,9 +355,9 @@ bp_status run_one(const bp_problem &q, const Plan &pl, const bp_params &p, uint8
                     r.msg_bytes = fmt_bytes(pl.lv[l].fmt);
                     r.units = 2.0 * sched.pairs(pi) * pl.lv[l].w * pl.lv[l].h * pl.L;
                     r.ms = 0.0f;
-                    r.bytes = pair_bytes(pl, l, store_c1);
+                    r.bytes = pair_bytes(pl, l, store_c1, ro_all);
                 }
-                lbytes += pair_bytes(pl, l, store_c1);
+                lbytes += pair_bytes(pl, l, store_c1, ro_all);
                 src_off = dst_off;
             }
         }
@@ -411,7 +414,7 @@ bp_status run_one(const bp_problem &q, const Plan &pl, const bp_params &p, uint8
                               sb, s)) != BP_OK)
             return st;
     }
-    if (q.disparity || q.soft_disparity) {
+    if ((q.disparity || q.soft_disparity) && !ro_all) {
         // After the fused readout only the last receivers' labels remain.
         const int mask = fuse_ro ? (1 << (K & 1)) : 3;
         if ((st = launch_readout(pl, mask, q.disparity, q.soft_disparity, p.temperature, ws, s)) != BP_OK) return st;
@@ -515,14 +518,15 @@ bool plan_run(const bp_problem *probs, int32_t count, const bp_params *p, Plan *
 // export, problem by problem (those with in_group[i] == g when in_group is
 // given).
 bp_status finish_batched(const bp_problem *probs, int32_t count, const Plan *plans, const bp_params &p,
-                         const bool *fuse, uint8_t *ws, hipStream_t s, const int *in_group = nullptr, int g = 0)
+                         const bool *fuse, uint8_t *ws, hipStream_t s, const int *in_group = nullptr, int g = 0,
+                         const bool *read_out = nullptr)
 {
     bp_status st = BP_OK;
     const int K = p.iters_per_level;
     for (int i = 0; i < count && st == BP_OK; ++i) {
         if (in_group && in_group[i] != g) continue;
         const bp_problem &q = probs[i];
-        if (q.disparity || q.soft_disparity) {
+        if ((q.disparity || q.soft_disparity) && !(read_out && read_out[i])) {
             const int mask = fuse[i] ? (1 << (K & 1)) : 3;
             st = launch_readout(plans[i], mask, q.disparity, q.soft_disparity, p.temperature, ws, s);
         }
@@ -586,6 +590,10 @@ bp_status run_batched_pairs(const bp_problem *probs, int32_t count, const Plan *
         const bool own_src = l < n - 1 && plans[i].lv[l].fmt != plans[i].lv[l + 1].fmt;
         return pair_schedule(plans[i], l, np, p.tau, ckpt != nullptr, own_src);
     };
+    // Whether the problem's last launch reads out both colours.
+    auto reads_out = [&](int i) {
+        return fuse[i] && stream_reads_out(schedule_of(0, i), probs[i].messages_out, ckpt);
+    };
     int *grp = new int[(size_t)n * count], ng = 1;
     for (int l = 0; l < n; ++l) {
         int g = 0;
@@ -608,6 +616,8 @@ bp_status run_batched_pairs(const bp_problem *probs, int32_t count, const Plan *
     PairEntry *dev = (PairEntry *)(ws + table_off);
     int *start = new int[nslot], *num = new int[nslot], *blocks = new int[nslot];
     size_t *lds = new size_t[nslot];
+    bool *done = new bool[count];
+    for (int i = 0; i < count; ++i) done[i] = reads_out(i);
     bool *ro = new bool[nslot], *exact = new bool[nslot];
     int e = 0;
     auto slot_of = [&](int l, int g, int q, int c) { return (((size_t)l * ng + g) * np + q) * ncls + c; };
@@ -658,7 +668,8 @@ bp_status run_batched_pairs(const bp_problem *probs, int32_t count, const Plan *
                         pe.a = make_pair_args(pl, l, kind, src, dst, store_c1, p.lambda, p.tau,
                                               rd ? probs[i].disparity : nullptr, ws, ck, ends,
                                               rd ? probs[i].soft_disparity : nullptr,
-                                              probs[i].soft_disparity ? 1.0f / p.temperature : 0.0f, sched.pairs(q));
+                                              probs[i].soft_disparity ? 1.0f / p.temperature : 0.0f, sched.pairs(q),
+                                              rd && done[i]);
                         pe.block0 = b0;
                         b0 += pair_blocks(pe.a);
                         const size_t lb = pair_lds_bytes(pe.a.tx, pe.a.ty, (int)pe.a.lp, fmt_bytes(pl.lv[l].fmt));
@@ -709,7 +720,7 @@ bp_status run_batched_pairs(const bp_problem *probs, int32_t count, const Plan *
                                                          host[start[slot]].a.cost_fmt, s);
                 }
             // The group's readout and export while its state is in the cache.
-            if (l == 0 && st == BP_OK) st = finish_batched(probs, count, plans, p, fuse, ws, s, grp, g);
+            if (l == 0 && st == BP_OK) st = finish_batched(probs, count, plans, p, fuse, ws, s, grp, g, done);
         }
     }
     delete[] host;
@@ -717,6 +728,7 @@ bp_status run_batched_pairs(const bp_problem *probs, int32_t count, const Plan *
     delete[] num;
     delete[] blocks;
     delete[] lds;
+    delete[] done;
     delete[] ro;
     delete[] exact;
     delete[] cls_of;

@@ -509,7 +509,7 @@ bp_status launch_iteration(const Plan &p, int l, int t, int src_mode, float lamb
 
 PairArgs make_pair_args(const Plan &p, int l, int src_kind, size_t src_off, size_t dst_off, bool write_c1,
                         float lambda, float tau, int32_t *disp, uint8_t *ws, uint8_t *ck, bool ck_c1, float *soft,
-                        float inv_t, int pairs)
+                        float inv_t, int pairs, bool ro0)
 {
     const Level &v = p.lv[l];
     PairArgs a;
@@ -540,6 +540,7 @@ PairArgs make_pair_args(const Plan &p, int l, int src_kind, size_t src_off, size
     a.disp = disp;
     a.soft = soft;
     a.inv_t = inv_t;
+    a.ro0 = ro0;
     a.w = v.w;
     a.h = v.h;
     a.wh = v.wh;
@@ -569,10 +570,10 @@ PairArgs make_pair_args(const Plan &p, int l, int src_kind, size_t src_off, size
 
 bp_status launch_iteration_pair(const Plan &p, int l, int src_kind, size_t src_off, size_t dst_off, bool write_c1,
                                 float lambda, float tau, int32_t *disp, uint8_t *ws, hipStream_t s, uint8_t *ck,
-                                bool ck_c1, float *soft, float inv_t, int pairs)
+                                bool ck_c1, float *soft, float inv_t, int pairs, bool ro0)
 {
     const PairArgs a = make_pair_args(p, l, src_kind, src_off, dst_off, write_c1, lambda, tau, disp, ws, ck, ck_c1,
-                                      soft, inv_t, pairs);
+                                      soft, inv_t, pairs, ro0);
     int S, R;
     pm_split(p.L, &S, &R);
     if (pairs > 1) return dispatch_iter_stream(a, p.lv[l].fmt, S, R, s);

@@ -129,7 +129,8 @@ enum { PAIR_SRC_OWN = 0, PAIR_SRC_PARENT = 1, PAIR_SRC_ZERO = 2 };
 bp_status launch_iteration_pair(const Plan &p, int l, int src_kind, size_t src_off, size_t dst_off, bool write_c1,
                                 float lambda, float tau, int32_t *disp, uint8_t *ws, hipStream_t s,
                                 uint8_t *ck = nullptr, bool ck_c1 = false, float *soft = nullptr,
-                                float inv_t = 0.0f, int pairs = 1);
+                                float inv_t = 0.0f, int pairs = 1,
+                                bool ro0 = false);
 
 // Half-sweep t of the finest level reading its incoming messages from `src`
 // (a saved state in the level's layout) and writing the receivers' slots
@@ -249,6 +250,7 @@ struct PairArgs {
     int32_t *disp;         // argmin labels of phase 2's senders, or NULL
     float *soft;           // their soft-argmin disparity (temperature 1 / inv_t), or NULL
     float inv_t;
+    int ro0;               // streamed launches: colour 0 is read out as well and no state is stored
     int w, h, wh;
     uint32_t blk, lp;      // this level's strides (pixel-major: ls = 1, ps = lp)
     uint32_t sblk, sps;    // strides of `src`
@@ -273,7 +275,8 @@ bp_status dispatch_iter_pm2(const PairArgs &a, int fmt, int S, int R, bool ro, h
 bool pair_supported(int S, int R);
 PairArgs make_pair_args(const Plan &p, int l, int src_kind, size_t src_off, size_t dst_off, bool write_c1,
                         float lambda, float tau, int32_t *disp, uint8_t *ws, uint8_t *ck = nullptr,
-                        bool ck_c1 = false, float *soft = nullptr, float inv_t = 0.0f, int pairs = 1);
+                        bool ck_c1 = false, float *soft = nullptr, float inv_t = 0.0f, int pairs = 1,
+                        bool ro0 = false);
 // Several pairs of half-sweeps in one launch (bp_iter_stream_impl.h).
 // PairSchedule: the launches that run a level's pairs, `ones` of one pair
 // (tiled), then `threes` of three and `twos` of two.  pair_schedule decides it
@@ -286,6 +289,9 @@ struct PairSchedule {
     int pairs(int i) const { return i < ones ? 1 : i < ones + threes ? 3 : 2; }   // of launch i
 };
 PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, bool even_count);
+// Whether the finest level's last launch can read out both colours (its state
+// then stays unwritten): it streams, and nothing reads the final state.
+bool stream_reads_out(const PairSchedule &s, bool exports, bool saves);
 void stream_shape(PairArgs *a, int S, int R);
 bp_status dispatch_iter_stream(const PairArgs &a, int fmt, int S, int R, hipStream_t s);
 // Window of the transform's near form: 1 (tau <= 2), 2 (tau <= 3), 0 (scans).

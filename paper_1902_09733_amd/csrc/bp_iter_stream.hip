@@ -14,12 +14,12 @@ namespace bpk {
 
 constexpr int kSlots = 256;   // blocks resident at a time: one per compute unit
 
-// Strips of a w-wide level for blocks of `nc` columns that run T half-sweeps:
-// tx columns with T - 1 more on each side (none beyond the grid), as wide as
-// the block allows.
-static int strip_width(int w, int nc, int T)
+// Strips of a w-wide level for blocks of `nc` columns that run `stages` stages
+// (half-sweeps, and the readout of colour 0): tx columns with stages - 1 more
+// on each side (none beyond the grid), as wide as the block allows.
+static int strip_width(int w, int nc, int stages)
 {
-    const int H = T - 1;
+    const int H = stages - 1;
     for (int n = 1;; ++n) {
         const int t = (w + n - 1) / n;
         if ((n == 1 ? t : n == 2 ? t + H : t + 2 * H) <= nc) return t;
@@ -28,12 +28,12 @@ static int strip_width(int w, int nc, int T)
 
 // Rows of a segment: the count of segments with the least time in the model
 //   rounds of resident blocks x steps of a block,
-// where a block of t rows takes t + 3 (T - 1) steps: short segments repeat the
-// T - 1 rows at their ends and fill the pipeline of stages anew, long ones
-// leave compute units idle.
-static int segment_rows(int h, int strips, int T)
+// where a block of t rows takes t + 3 (stages - 1) steps: short segments repeat
+// the rows at their ends and fill the pipeline of stages anew, long ones leave
+// compute units idle.
+static int segment_rows(int h, int strips, int stages)
 {
-    const int H = T - 1, most = std::max(1, std::min(h, 4 * kSlots / strips));
+    const int H = stages - 1, most = std::max(1, std::min(h, 4 * kSlots / strips));
     int64_t best = -1;
     int ty = h;
     for (int k = 1; k <= most; ++k) {
@@ -121,12 +121,21 @@ PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, 
     return s;
 }
 
+// The extra stage against colour 0's state stored and a readout pass over it,
+// whole frames: 676 x 380 x 64 FP32 454 -> 431 us, 1352 x 760 x 128 FP32 2591 ->
+// 2327, in bfloat16 with soft disparities 2823 -> 2758, eight frames in FP16
+// 5368 -> 5267.
+bool stream_reads_out(const PairSchedule &s, bool exports, bool saves)
+{
+    return !exports && !saves && s.count() > 0 && s.pairs(s.count() - 1) > 1;
+}
+
 void stream_shape(PairArgs *a, int SEGV, int R)
 {
-    const int T = 2 * a->pairs;
-    a->tx = strip_width(a->w, stream_columns(SEGV, R), T);
+    const int stages = 2 * a->pairs + (a->ro0 ? 1 : 0);
+    a->tx = strip_width(a->w, stream_columns(SEGV, R), stages);
     a->tiles_x = (a->w + a->tx - 1) / a->tx;
-    a->ty = segment_rows(a->h, a->tiles_x, T);
+    a->ty = segment_rows(a->h, a->tiles_x, stages);
     a->ntiles = a->tiles_x * ((a->h + a->ty - 1) / a->ty);
     a->per_xcd = (a->ntiles + 7) / 8;
 }

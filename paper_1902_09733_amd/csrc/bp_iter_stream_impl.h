@@ -171,17 +171,21 @@ constexpr uint32_t kNowhere = 0xffffff00u;
 
 // END: 0 a launch inside a level; 1 its last one, which stores colour 1's
 // incoming rows; 2 the finest level's last one, which reads out colour 1 (and
-// stores its rows when asked).
+// stores its rows when asked); 3 the same where nothing reads the final state:
+// it reads out colour 0 too, in one more stage, and stores labels only (a
+// readout pass reads colour 0's state and costs: 21 us at 676 x 380 x 64 and
+// 215 at 1352 x 760 x 128, in FP32).
 template <int SEG, int R, typename S, int P, int NW, int CF, int NEAR, int END>
 __global__ void __launch_bounds__(NW * 64) k_iter_stream(const PairArgs a)
 {
-    constexpr int T = 2 * P, H = T - 1;
+    constexpr int T = 2 * P, NS = END == 3 ? T + 1 : T, H = NS - 1;   // half-sweeps, stages, columns repeated
+    constexpr int PO = END == 3 ? P + 1 : P;             // odd stages
     constexpr int CPW = 64 / SEG, NC = NW * CPW;         // columns per wave and per block
     constexpr int MW = msg_words<S, R>, CW = cost_words<R, CF>;
     constexpr uint32_t CB = cost_bytes_of<R, CF>, MB = S::bytes;
     constexpr int ROW = SEG * MW;                        // words of an exchange row
     constexpr int BND = NC * 2 * ROW;                    // words of a boundary's exchange rows
-    extern __shared__ __attribute__((aligned(16))) uint32_t xch[];                    // [T - 1 boundaries][NC][2 sides][ROW]
+    extern __shared__ __attribute__((aligned(16))) uint32_t xch[];                    // [NS - 1 boundaries][NC][2 sides][ROW]
 
     // Tile of the block: consecutive tiles per XCD (blocks b, b + 8, ... run
     // on one), strips fastest, so that neighbours' shared columns meet in
@@ -200,8 +204,8 @@ __global__ void __launch_bounds__(NW * 64) k_iter_stream(const PairArgs a)
     const bool has_l = x > 0 && in_x, has_r = x < a.w - 1;
     const uint32_t lp = a.lp;
 
-    // Rows of stage st (1-based): the segment and T - st more on each side.
-    auto row_on = [&](int st, int y) BP_INLINE { return y >= max(0, ya - (T - st)) && y < min(a.h, yb + (T - st)); };
+    // Rows of stage st (1-based): the segment and NS - st more on each side.
+    auto row_on = [&](int st, int y) BP_INLINE { return y >= max(0, ya - (NS - st)) && y < min(a.h, yb + (NS - st)); };
 
     // Bytes of a pixel row of one colour (and slot) of the cost, the level's
     // states and the source state, and of a colour-and-slot block of each.
@@ -258,9 +262,9 @@ __global__ void __launch_bounds__(NW * 64) k_iter_stream(const PairArgs a)
     uint32_t *const my_row = xch + (col * 2) * ROW;      // + boundary * BND + side * ROW
 
     // Messages held between stages b + 1 and b + 2, as stored.
-    uint32_t up[T - 1][MW], dn[T - 1][MW], dd[T - 1][MW];
+    uint32_t up[NS - 1][MW], dn[NS - 1][MW], dd[NS - 1][MW];
 #pragma unroll
-    for (int b = 0; b < T - 1; ++b)
+    for (int b = 0; b < NS - 1; ++b)
 #pragma unroll
         for (int i = 0; i < MW; ++i) up[b][i] = dn[b][i] = dd[b][i] = 0u;
 
@@ -273,20 +277,22 @@ __global__ void __launch_bounds__(NW * 64) k_iter_stream(const PairArgs a)
 #pragma unroll
         for (int k = 0; k < 4; ++k) unpack_row<S, R>(mw[k], m[k]);
         const bool has_u = !CHECK || y > 0, has_d = !CHECK || y < a.h - 1;
-        if constexpr (ST == T && END == 2) {
+        if constexpr (ST >= T && END >= 2) {
             // Labels of the row's columns (no label array, no row); lane 0 of
             // a column stores them.
             float bel[R], sv;
             int bi;
             pm_belief<R>(c, m, bel);
             pm_readout<SEG, R, true>(bel, f0, a.L, a.soft != nullptr, a.inv_t, bi, sv);
-            const uint32_t row = (uint32_t)a.w * 4u, at = out_x && s == 0 ? (uint32_t)x * 4u : kNowhere;
+            const uint32_t row = ST == NS || (y >= ya && y < yb) ? (uint32_t)a.w * 4u : 0u;
+            const uint32_t at = out_x && s == 0 ? (uint32_t)x * 4u : kNowhere;
             __builtin_amdgcn_raw_buffer_store_b32((uint32_t)bi, make_rsrc(a.disp + (size_t)y * a.w, a.disp ? row : 0u),
                                                   at, 0, 0);
             __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sv),
                                                   make_rsrc(a.soft + (size_t)y * a.w, a.soft ? row : 0u), at, 0, 0);
         }
-        if constexpr (ST == T && END != 0) {
+        if constexpr (ST == NS && END == 3) return;
+        if constexpr (ST == T && (END == 1 || END == 2)) {
             const uint32_t lanes[4] = {has_l ? wr_c : kNowhere, has_r ? wr_c : kNowhere, wr_c, wr_c};
             const bool has[4] = {true, true, has_u, has_d};
 #pragma unroll
@@ -301,7 +307,7 @@ __global__ void __launch_bounds__(NW * 64) k_iter_stream(const PairArgs a)
             pm_h<R>(c, m, k, h);
             pm_transform<SEG, R, true, NEAR>(h, s, f0, a.L, a.lambda, a.lt, o);
             pack_row<S, R>(o, w);
-            if constexpr (ST == T) {
+            if constexpr (ST == NS) {
                 const int ny = k == 2 ? y - 1 : k == 3 ? y + 1 : y;
                 const bool has = k == 2 ? has_u : k == 3 ? has_d : true;
                 st_words<MW>(row_at(a.dst, (uint32_t)(k ^ 1) * mblk + (uint32_t)ny * mrow, mrow, has),
@@ -322,7 +328,7 @@ __global__ void __launch_bounds__(NW * 64) k_iter_stream(const PairArgs a)
 
     // Stage 1's rows of the next odd step; the costs and the left and right
     // rows of the next step's later stages.
-    uint32_t c1[CW], m1[4][MW], cn[P][CW], l[P][MW], r[P][MW];
+    uint32_t c1[CW], m1[4][MW], cn[PO][CW], l[PO][MW], r[PO][MW];
 
     // One step of the wave at row y1: odd stages (1, 3, ...) or even ones,
     // the later ones first, so that stage T's stores are long issued when
@@ -330,20 +336,20 @@ __global__ void __launch_bounds__(NW * 64) k_iter_stream(const PairArgs a)
     // ahead may lie outside its range or on the grid's first or last row.
     auto step = [&](auto odd_tag, auto check, int y1) BP_INLINE {
         constexpr bool ODD = decltype(odd_tag)::value, CHECK = decltype(check)::value;
-        uint32_t cc[P][CW];
+        uint32_t cc[PO][CW];
 #pragma unroll
-        for (int q = 0; q < P; ++q)
+        for (int q = 0; q < PO; ++q)
 #pragma unroll
             for (int i = 0; i < CW; ++i) cc[q][i] = cn[q][i];
         // Costs of the next step's later stages.
 #pragma unroll
-        for (int q = ODD ? 0 : 1; q < P; ++q)
+        for (int q = ODD ? 0 : 1; q < (ODD ? P : PO); ++q)
             load_cost(check, ODD ? 1 : 0, ODD ? 2 * q + 2 : 2 * q + 1, y1 + 1 - (ODD ? 4 * q + 2 : 4 * q), cn[q]);
         // Stage 2q + 1 (odd steps) or 2q + 2.
         auto later = [&](auto q_tag) BP_INLINE {
             constexpr int q = decltype(q_tag)::value, ST = ODD ? 2 * q + 1 : 2 * q + 2, b = ST - 2;
             const int y = y1 - 2 * (ST - 1);
-            if constexpr (ST < T) {
+            if constexpr (ST < NS) {
 #pragma unroll
                 for (int i = 0; i < MW; ++i) dd[ST - 1][i] = dn[ST - 1][i];
             }
@@ -361,6 +367,7 @@ __global__ void __launch_bounds__(NW * 64) k_iter_stream(const PairArgs a)
             }
             visit(std::integral_constant<int, ST>{}, check, y, cc[q], mw);
         };
+        if constexpr (ODD && PO > P) later(std::integral_constant<int, P>{});
         if constexpr (P > 2) later(std::integral_constant<int, (P > 2 ? 2 : 1)>{});
         if constexpr (P > 1) later(std::integral_constant<int, (P > 1 ? 1 : 0)>{});
         if constexpr (ODD) {
@@ -374,7 +381,7 @@ __global__ void __launch_bounds__(NW * 64) k_iter_stream(const PairArgs a)
         // Rows of the next step's later stages: written in the step before
         // this one, and written again only in the next one.
 #pragma unroll
-        for (int q = ODD ? 0 : 1; q < P; ++q) {
+        for (int q = ODD ? 0 : 1; q < (ODD ? P : PO); ++q) {
             const uint32_t *row = my_row + (ODD ? 2 * q : 2 * q - 1) * BND;
             lds_get<SEG, MW>(row, s, l[q]);
             lds_get<SEG, MW>(row + ROW, s, r[q]);
@@ -388,20 +395,20 @@ __global__ void __launch_bounds__(NW * 64) k_iter_stream(const PairArgs a)
 
     // Rows that no column writes (beyond the grid, and the block's first and
     // last column) read as zero.
-    for (int i = (int)threadIdx.x; i < (T - 1) * BND; i += NW * 64) xch[i] = 0u;
+    for (int i = (int)threadIdx.x; i < (NS - 1) * BND; i += NW * 64) xch[i] = 0u;
     __syncthreads();
 
     // Steps ybeg .. ybeg + n - 1 (n even), in twos of an odd and an even step;
     // the waves whose first step is an even one start and end with one alone.
     const int ybeg = max(0, ya - H);
-    const int n = (yb - 1 + 2 * (T - 1) - ybeg + 2) & ~1, yend = ybeg + n;
+    const int n = (yb - 1 + 2 * (NS - 1) - ybeg + 2) & ~1, yend = ybeg + n;
     const bool odd_first = (((x0 + (wv & 1)) + ybeg) & 1) == 0;
 #pragma unroll
-    for (int q = 0; q < P; ++q)
+    for (int q = 0; q < PO; ++q)
 #pragma unroll
         for (int i = 0; i < CW; ++i) cn[q][i] = 0u;
 #pragma unroll
-    for (int q = 0; q < P; ++q)
+    for (int q = 0; q < PO; ++q)
 #pragma unroll
         for (int i = 0; i < MW; ++i) l[q][i] = r[q][i] = 0u;
     int y1 = ybeg;
@@ -409,7 +416,7 @@ __global__ void __launch_bounds__(NW * 64) k_iter_stream(const PairArgs a)
     if (!odd_first) step(Even{}, Check{}, y1++);
     // In steps [free_lo, free_hi) every stage's row, and stage 1's two steps
     // ahead, is in its range and inside the grid.
-    const int free_lo = max(ya, 1) + 2 * (T - 1), free_hi = min(a.h - 1, yb + H) - 2;
+    const int free_lo = max(ya, 1) + 2 * (NS - 1), free_hi = min(a.h - 1, yb + H) - 2;
 #pragma unroll 1
     while (y1 + 1 < yend && y1 < free_lo) {
         step(Odd{}, Check{}, y1);
@@ -436,10 +443,11 @@ template <int SEG, int R, typename S, int P, int CF, int NEAR>
 static bp_status launch_stream_pairs(const PairArgs &a, hipStream_t st)
 {
     constexpr int NW = stream_waves(R), NC = NW * (64 / SEG);
-    constexpr size_t lds = (size_t)(2 * P - 1) * NC * 2 * SEG * msg_words<S, R> * 4;
-    static_assert(lds <= 160 * 1024, "exchange rows exceed the LDS");
+    constexpr size_t row = (size_t)NC * 2 * SEG * msg_words<S, R> * 4, lds = (2 * P - 1) * row;
+    static_assert(lds + row <= 160 * 1024, "exchange rows exceed the LDS");
     const unsigned grid = (unsigned)(8 * a.per_xcd);
-    if (a.disp || a.soft) k_iter_stream<SEG, R, S, P, NW, CF, NEAR, 2><<<grid, NW * 64, lds, st>>>(a);
+    if (a.ro0) k_iter_stream<SEG, R, S, P, NW, CF, NEAR, 3><<<grid, NW * 64, lds + row, st>>>(a);
+    else if (a.disp || a.soft) k_iter_stream<SEG, R, S, P, NW, CF, NEAR, 2><<<grid, NW * 64, lds, st>>>(a);
     else if (a.write_c1) k_iter_stream<SEG, R, S, P, NW, CF, NEAR, 1><<<grid, NW * 64, lds, st>>>(a);
     else k_iter_stream<SEG, R, S, P, NW, CF, NEAR, 0><<<grid, NW * 64, lds, st>>>(a);
     return launch_status();
