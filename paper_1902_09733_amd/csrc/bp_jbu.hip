@@ -1,7 +1,8 @@
 // a7 on gfx950: joint bilateral upsampling of the disparity (Eq. 2), with an
 // optional fused triangulation of every output pixel (Eq. 3).
 //
-// A 256-thread block owns 16 x 16 full-resolution pixels.  The low-resolution
+// A 256-thread block owns 16 x 16 full-resolution pixels (16 x 32 with two rows
+// per thread).  The low-resolution
 // taps every pixel of the block can reach are staged once in LDS, one 16-byte
 // record each: the guide sample I_q at scale*q + scale/2 as FP16 channel pairs
 // (exact for 8-bit values), -|I_q|^2 and the tap's disparity as floats.  The
@@ -60,7 +61,7 @@ __device__ __forceinline__ h2_t bits_h2(uint32_t u) { return __builtin_bit_cast(
 // from an integer, beyond the error of the product.
 __device__ __forceinline__ int div_small(int a, float rb) { return (int)(((float)a + 0.5f) * rb); }
 
-template <int R, int C, bool PTS>
+template <int R, int C, bool PTS, int NY>
 __global__ void __launch_bounds__(256) k_jbu(const int32_t *__restrict__ disp, int wl, int hl,
                                             const uint8_t *__restrict__ guide, int wh, int hh, int64_t stride,
                                             int s, float rs, float ksp, float krg, float *__restrict__ out,
@@ -73,11 +74,12 @@ __global__ void __launch_bounds__(256) k_jbu(const int32_t *__restrict__ disp, i
     constexpr int NT = 2 * R + 1;
     // Separable spatial terms of the block's 16 columns and 16 rows, per
     // window column / row: the x exponent, and exp2 of the y exponent.
-    __shared__ float t_sx[kTile * NT], t_wy[kTile * NT];
-    const int bx0 = blockIdx.x * kTile, by0 = blockIdx.y * kTile;
+    constexpr int ROWS = kTile * NY;
+    __shared__ float t_sx[kTile * NT], t_wy[ROWS * NT];
+    const int bx0 = blockIdx.x * kTile, by0 = blockIdx.y * ROWS;
     const int qx0 = bx0 / s - R, qy0 = by0 / s - R;
     const int tw = (bx0 + kTile - 1) / s - bx0 / s + 1 + 2 * R;
-    const int th = (by0 + kTile - 1) / s - by0 / s + 1 + 2 * R;
+    const int th = (by0 + ROWS - 1) / s - by0 / s + 1 + 2 * R;
     const float rtw = __builtin_amdgcn_rcpf((float)tw);
     for (int i = threadIdx.x; i < tw * th; i += 256) {
         const int ty = div_small(i, rtw), tx = i - ty * tw;
@@ -98,7 +100,7 @@ __global__ void __launch_bounds__(256) k_jbu(const int32_t *__restrict__ disp, i
         t_q[ty * kMaxTap + tx] = r;
     }
     // s * (p_lo - q) = phase + 0.5 - s/2 - s*dq for window offset dq = i - R.
-    for (int i = threadIdx.x; i < 2 * kTile * NT; i += 256) {
+    for (int i = threadIdx.x; i < (kTile + ROWS) * NT; i += 256) {
         const int y = i >= kTile * NT, e = i - y * (kTile * NT), c = e / NT, k = e - c * NT;
         const int p = (y ? by0 : bx0) + c;
         const float t = (float)(p - s * div_small(p, rs)) + 0.5f - 0.5f * (float)s - (float)(s * (k - R));
@@ -107,117 +109,152 @@ __global__ void __launch_bounds__(256) k_jbu(const int32_t *__restrict__ disp, i
         else t_sx[e] = v;
     }
     __syncthreads();
-    const int col = (int)(threadIdx.x % kTile), rowi = (int)(threadIdx.x / kTile);
-    const int px = bx0 + col, py = by0 + rowi;
-    if (px >= wh || py >= hh) return;
-    const uint32_t ip = guide_px<C>(guide, stride, px, py);
-    const int np = (int)__builtin_amdgcn_udot4(ip, ip, 0u, false);
+    const int col = (int)(threadIdx.x % kTile), rowi = (int)(threadIdx.x / kTile) * NY;
+    const int px = bx0 + col, py0 = by0 + rowi;
+    if (px >= wh || py0 >= hh) return;                  // hh is a multiple of s, so of NY
+    const int cx = div_small(px, rs), cy = div_small(py0, rs);
+    const int ox = cx - R - qx0, oy = cy - R - qy0;     // tile coordinates of the window corner
     // Pixel side of the dot products: 2 I_p (exact in FP16 up to 510) and
-    // -floor(|I_p|^2 / 256) (at most 762) against the tap's 256.
-    h2_t pa2, pb2;
-    if constexpr (C == 3) {
-        pa2 = bits_h2(h2_bits(2.0f * (float)(ip & 255u), 2.0f * (float)((ip >> 8) & 255u)));
-        pb2 = bits_h2(h2_bits(2.0f * (float)(ip >> 16), -(float)(np >> 8)));
-    } else {
-        pa2 = bits_h2(h2_bits(2.0f * (float)ip, -(float)(np >> 8)));
-        pb2 = pa2;
+    // -floor(|I_p|^2 / 256) (at most 762) against the tap's 256; and the x term
+    // of the exponent: spatial x exponent less krg * the low byte of |I_p|^2.
+    h2_t pa2[NY], pb2[NY];
+    float ex[NY][NT];
+#pragma unroll
+    for (int k = 0; k < NY; ++k) {
+        const uint32_t ip = guide_px<C>(guide, stride, px, py0 + k);
+        const int np = (int)__builtin_amdgcn_udot4(ip, ip, 0u, false);
+        if constexpr (C == 3) {
+            pa2[k] = bits_h2(h2_bits(2.0f * (float)(ip & 255u), 2.0f * (float)((ip >> 8) & 255u)));
+            pb2[k] = bits_h2(h2_bits(2.0f * (float)(ip >> 16), -(float)(np >> 8)));
+        } else {
+            pa2[k] = bits_h2(h2_bits(2.0f * (float)ip, -(float)(np >> 8)));
+            pb2[k] = pa2[k];
+        }
+        const float np_lo = krg * (float)(np & 255);
+#pragma unroll
+        for (int i = 0; i < NT; ++i) ex[k][i] = t_sx[col * NT + i] - np_lo;
     }
-    const float np_lo = krg * (float)(np & 255);
-    const int cx = div_small(px, rs), cy = div_small(py, rs);
-    const int ox = cx - R - qx0, oy = cy - R - qy0;   // tile coordinates of the window corner
-    // Separable spatial exponents: s * (p_lo - q) = phase + 0.5 - s/2 - s*dq.
-    const float fx = (float)(px - s * cx) + 0.5f - 0.5f * (float)s;
-    const float fy = (float)(py - s * cy) + 0.5f - 0.5f * (float)s;
     // Range part of a tap's exponent before scaling, from its record:
     // 2 I_p.I_q - |I_q|^2 - 256 floor(|I_p|^2 / 256), an exact integer (-inf
     // outside the grid).
-    auto range = [&](const uint4 &q) {
-        float r = __builtin_amdgcn_fdot2(pa2, bits_h2(q.x), __uint_as_float(q.z), false);
-        if constexpr (C == 3) r = __builtin_amdgcn_fdot2(pb2, bits_h2(q.y), r, false);
+    auto range = [&](int k, const uint4 &q) {
+        float r = __builtin_amdgcn_fdot2(pa2[k], bits_h2(q.x), __uint_as_float(q.z), false);
+        if constexpr (C == 3) r = __builtin_amdgcn_fdot2(pb2[k], bits_h2(q.y), r, false);
         return r;
     };
-    // x term of the exponent: spatial x exponent less krg * the low byte of |I_p|^2.
-    float ex[NT];
+    float num[NY], den[NY];
 #pragma unroll
-    for (int i = 0; i < NT; ++i) ex[i] = t_sx[col * NT + i] - np_lo;
-    float num = 0.0f, den = 0.0f;
+    for (int k = 0; k < NY; ++k) num[k] = den[k] = 0.0f;
 #pragma unroll
     for (int dy = 0; dy < NT; ++dy) {
-        const float wy = t_wy[rowi * NT + dy];
-        float rn = 0.0f, rd = 0.0f;
+        float rn[NY], rd[NY];
+#pragma unroll
+        for (int k = 0; k < NY; ++k) rn[k] = rd[k] = 0.0f;
 #pragma unroll
         for (int dx = 0; dx < NT; ++dx) {
             const uint4 q = t_q[(oy + dy) * kMaxTap + ox + dx];
-            const float w = __builtin_amdgcn_exp2f(fmaf(range(q), krg, ex[dx]));
-            rn = fmaf(w, __uint_as_float(q.w), rn);
-            rd += w;
+#pragma unroll
+            for (int k = 0; k < NY; ++k) {
+                const float w = __builtin_amdgcn_exp2f(fmaf(range(k, q), krg, ex[k][dx]));
+                rn[k] = fmaf(w, __uint_as_float(q.w), rn[k]);
+                rd[k] += w;
+            }
         }
-        num = fmaf(wy, rn, num);
-        den = fmaf(wy, rd, den);
+#pragma unroll
+        for (int k = 0; k < NY; ++k) {
+            const float wy = t_wy[(rowi + k) * NT + dy];
+            num[k] = fmaf(wy, rn[k], num[k]);
+            den[k] = fmaf(wy, rd[k], den[k]);
+        }
     }
-    if (!(den >= 0x1p-60f)) {
-        // Every weight is tiny: the same sums relative to the tap of largest
-        // exponent (finite, since the pixel's own cell is in the grid), with
-        // the range difference to it taken exactly before scaling so that
-        // exponents far below zero keep their precision.
-        float emax = -__builtin_huge_valf(), rm = 0.0f, sm = 0.0f;
+#pragma unroll
+    for (int k = 0; k < NY; ++k) {
+        const int py = py0 + k;
+        if (!(den[k] >= 0x1p-60f)) {
+            // Every weight is tiny: the same sums relative to the tap of largest
+            // exponent (finite, since the pixel's own cell is in the grid), with
+            // the range difference to it taken exactly before scaling so that
+            // exponents far below zero keep their precision.
+            // Separable spatial exponents: s * (p_lo - q) = phase + 0.5 - s/2 - s*dq.
+            const float fx = (float)(px - s * cx) + 0.5f - 0.5f * (float)s;
+            const float fy = (float)(py - s * cy) + 0.5f - 0.5f * (float)s;
+            float emax = -__builtin_huge_valf(), rm = 0.0f, sm = 0.0f;
 #pragma unroll 1
-        for (int dy = 0; dy < NT; ++dy) {
-            const float ty = fy - (float)(s * (dy - R)), sy = -(ty * ty * ksp);
+            for (int dy = 0; dy < NT; ++dy) {
+                const float ty = fy - (float)(s * (dy - R)), sy = -(ty * ty * ksp);
 #pragma unroll 1
-            for (int dx = 0; dx < NT; ++dx) {
-                const float tx = fx - (float)(s * (dx - R)), sp = sy - tx * tx * ksp;
-                const float r = range(t_q[(oy + dy) * kMaxTap + ox + dx]), e = fmaf(r, krg, sp);
-                if (e > emax) {
-                    emax = e;
-                    rm = r;
-                    sm = sp;
+                for (int dx = 0; dx < NT; ++dx) {
+                    const float tx = fx - (float)(s * (dx - R)), sp = sy - tx * tx * ksp;
+                    const float r = range(k, t_q[(oy + dy) * kMaxTap + ox + dx]), e = fmaf(r, krg, sp);
+                    if (e > emax) {
+                        emax = e;
+                        rm = r;
+                        sm = sp;
+                    }
+                }
+            }
+            num[k] = 0.0f;
+            den[k] = 0.0f;
+#pragma unroll 1
+            for (int dy = 0; dy < NT; ++dy) {
+                const float ty = fy - (float)(s * (dy - R)), sy = -(ty * ty * ksp);
+#pragma unroll 1
+                for (int dx = 0; dx < NT; ++dx) {
+                    const float tx = fx - (float)(s * (dx - R)), sp = sy - tx * tx * ksp;
+                    const uint4 q = t_q[(oy + dy) * kMaxTap + ox + dx];
+                    const float w = __builtin_amdgcn_exp2f(fmaf(range(k, q) - rm, krg, sp - sm));
+                    num[k] = fmaf(w, __uint_as_float(q.w), num[k]);
+                    den[k] += w;
                 }
             }
         }
-        num = 0.0f;
-        den = 0.0f;
-#pragma unroll 1
-        for (int dy = 0; dy < NT; ++dy) {
-            const float ty = fy - (float)(s * (dy - R)), sy = -(ty * ty * ksp);
-#pragma unroll 1
-            for (int dx = 0; dx < NT; ++dx) {
-                const float tx = fx - (float)(s * (dx - R)), sp = sy - tx * tx * ksp;
-                const uint4 q = t_q[(oy + dy) * kMaxTap + ox + dx];
-                const float w = __builtin_amdgcn_exp2f(fmaf(range(q) - rm, krg, sp - sm));
-                num = fmaf(w, __uint_as_float(q.w), num);
-                den += w;
+        // den >= 2^-60 here (>= 1 after the second pass): a normal number.
+        const float dp = num[k] * __builtin_amdgcn_rcpf(den[k]);
+        if (out) out[(int64_t)py * wh + px] = dp;
+        if constexpr (PTS) {
+            const float d = (float)s * dp;
+            float x = __builtin_nanf(""), y = x, z = x;
+            if (d > 0.0f) {
+                const float b = pa.baseline / d;
+                x = b * ((float)px - pa.u0);
+                y = b * ((float)py - pa.v0) * pa.dv_du;
+                z = b * pa.f_du;
             }
+            float *o = pa.xyz + ((int64_t)py * wh + px) * 3;
+            o[0] = x;
+            o[1] = y;
+            o[2] = z;
         }
-    }
-    // den >= 2^-60 here (>= 1 after the second pass): a normal number.
-    const float dp = num * __builtin_amdgcn_rcpf(den);
-    if (out) out[(int64_t)py * wh + px] = dp;
-    if constexpr (PTS) {
-        const float d = (float)s * dp;
-        float x = __builtin_nanf(""), y = x, z = x;
-        if (d > 0.0f) {
-            const float k = pa.baseline / d;
-            x = k * ((float)px - pa.u0);
-            y = k * ((float)py - pa.v0) * pa.dv_du;
-            z = k * pa.f_du;
-        }
-        float *o = pa.xyz + ((int64_t)py * wh + px) * 3;
-        o[0] = x;
-        o[1] = y;
-        o[2] = z;
     }
 }
+
+template <int R, int C, int NY>
+static void launch_jbu(const int32_t *disp_lo, int wl, int hl, const uint8_t *guide, int wh, int hh, int64_t stride,
+                       float ksp, float krg, float *out, const PointArgs &pa, hipStream_t st)
+{
+    const int s = wh / wl;
+    const float rs = 1.0f / (float)s;
+    const dim3 grid((unsigned)((wh + kTile - 1) / kTile), (unsigned)((hh + kTile * NY - 1) / (kTile * NY)));
+    if (pa.xyz) k_jbu<R, C, true, NY><<<grid, 256, 0, st>>>(disp_lo, wl, hl, guide, wh, hh, stride, s, rs, ksp, krg, out, pa);
+    else k_jbu<R, C, false, NY><<<grid, 256, 0, st>>>(disp_lo, wl, hl, guide, wh, hh, stride, s, rs, ksp, krg, out, pa);
+}
+
+// Pixels per thread (NY): two rows of a cell share their taps' records and the
+// setup, which is a quarter of the issue slots at R = 4 (RGB, s = 4, one / two
+// rows: 2704 x 1520 R 4 79.2 / 72.3 us, R 2 33.5 / 29.4, R 1 22.7 / 18.4; 1600 x
+// 900 R 4 31.7 / 30.7).  Small outputs need the threads (1000 x 560 R 4 15.8 /
+// 16.6), and with one channel a wide window's sums outweigh the setup (2704 x
+// 1520 R 4 62.3 / 62.5, R 2 28.9 / 25.6).  Four rows: 77.7, no better anywhere.
+constexpr int kRowsRadius = 4, kRowsRadiusGrey = 2;
+constexpr int64_t kRowsPixels = 1200000;
 
 bp_status launch_upsample(const int32_t *disp_lo, int wl, int hl, const uint8_t *guide, int wh, int hh, int ch,
                           int64_t stride, float sigma_s, float sigma_r, int radius, float *out, const bp_camera *cam,
                           float *xyz, hipStream_t st)
 {
-    const int s = wh / wl;
     const float log2e = 1.4426950408889634f;
     const float ksp = log2e / (2.0f * sigma_s * sigma_s);
     const float krg = log2e / (2.0f * sigma_r * sigma_r);
-    const float rs = 1.0f / (float)s;
     PointArgs pa{xyz, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
     if (cam) {
         pa.baseline = cam->baseline;
@@ -226,17 +263,16 @@ bp_status launch_upsample(const int32_t *disp_lo, int wl, int hl, const uint8_t 
         pa.u0 = cam->u0;
         pa.v0 = cam->v0;
     }
-    const bool pts = xyz != nullptr;
-    dim3 grid((wh + kTile - 1) / kTile, (hh + kTile - 1) / kTile);
-#define BP_JBU_CASE(RV)                                                                                       \
-    case RV:                                                                                                  \
-        if (ch == 1) {                                                                                        \
-            if (pts) k_jbu<RV, 1, true><<<grid, 256, 0, st>>>(disp_lo, wl, hl, guide, wh, hh, stride, s, rs, ksp, krg, out, pa); \
-            else k_jbu<RV, 1, false><<<grid, 256, 0, st>>>(disp_lo, wl, hl, guide, wh, hh, stride, s, rs, ksp, krg, out, pa);    \
-        } else {                                                                                              \
-            if (pts) k_jbu<RV, 3, true><<<grid, 256, 0, st>>>(disp_lo, wl, hl, guide, wh, hh, stride, s, rs, ksp, krg, out, pa); \
-            else k_jbu<RV, 3, false><<<grid, 256, 0, st>>>(disp_lo, wl, hl, guide, wh, hh, stride, s, rs, ksp, krg, out, pa);    \
-        }                                                                                                     \
+    const bool two = (wh / wl) % 2 == 0 && (int64_t)wh * hh >= kRowsPixels;
+#define BP_JBU(RV, CV)                                                                                       \
+    if (RV <= (CV == 1 ? kRowsRadiusGrey : kRowsRadius) && two)                                              \
+        launch_jbu<RV, CV, (RV <= (CV == 1 ? kRowsRadiusGrey : kRowsRadius) ? 2 : 1)>(                       \
+            disp_lo, wl, hl, guide, wh, hh, stride, ksp, krg, out, pa, st);                                  \
+    else launch_jbu<RV, CV, 1>(disp_lo, wl, hl, guide, wh, hh, stride, ksp, krg, out, pa, st);
+#define BP_JBU_CASE(RV)                                                                                      \
+    case RV:                                                                                                 \
+        if (ch == 1) { BP_JBU(RV, 1) }                                                                       \
+        else { BP_JBU(RV, 3) }                                                                               \
         break;
     switch (radius) {
         BP_JBU_CASE(0)
@@ -251,6 +287,7 @@ bp_status launch_upsample(const int32_t *disp_lo, int wl, int hl, const uint8_t 
     default: return BP_ERR_UNSUPPORTED;
     }
 #undef BP_JBU_CASE
+#undef BP_JBU
     return launch_status();
 }
 
