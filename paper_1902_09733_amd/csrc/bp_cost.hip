@@ -7,10 +7,13 @@
 // into LDS, then every label plane is written with coalesced 1 KB row stores.
 //
 // bp_run from a pair: the downsampled pair is first packed (one 32-bit word
-// per pixel) into the workspace, then the data term is written straight into
+// per pixel) into the workspace (pixel-major levels of an undownsampled pair
+// read the frames themselves), then the data term is written straight into
 // the finest level's colour-split layout (pixel-major or label-major), so the
 // planar volume never exists.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "bp_internal.h"
 #include "bp_levels.h"
@@ -37,28 +40,35 @@ __device__ __forceinline__ uint32_t pixel_ds(const uint8_t *__restrict__ img, in
 
 constexpr int kSeg = 256;
 
+// How a pixel pair's absolute differences become the data term: one channel's,
+// three channels' mean rounded half up as the frames' bytes are, or exactly.
+enum { AD_GREY = 0, AD_ROUNDED = 1, AD_EXACT = 2 };
+constexpr int ad_channels(int mode) { return mode == AD_GREY ? 1 : 3; }
+
 // Data term of Eq. 1 for packed left/right pixels lv, rv (label d with x - d >= 0).
-template <int C>
-__device__ __forceinline__ float ad_cost(uint32_t lv, uint32_t rv, int rgb_mode, float trunc)
+template <int MODE>
+__device__ __forceinline__ float ad_cost(uint32_t lv, uint32_t rv, float trunc)
 {
+    const uint32_t sum = __builtin_amdgcn_sad_u8(lv, rv, 0u);   // at most 765; unused bytes are zero
     float a;
-    if constexpr (C == 1) {
-        a = (float)abs((int)lv - (int)rv);
+    if constexpr (MODE == AD_GREY) {
+        a = (float)sum;
+    } else if constexpr (MODE == AD_ROUNDED) {
+        a = (float)(((sum + 1u) * 21846u) >> 16);               // (sum + 1) / 3 up to 766
     } else {
-        int sum = 0;
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch)
-            sum += abs((int)((lv >> (8 * ch)) & 0xffu) - (int)((rv >> (8 * ch)) & 0xffu));
-        a = rgb_mode == 0 ? (float)((sum + 1) / 3) : (float)sum / 3.0f;
+        // sum / 3 correctly rounded: quotient, remainder (exact), correction.
+        const float n = (float)sum, third = 1.0f / 3.0f, q = n * third;
+        a = fmaf(fmaf(-3.0f, q, n), third, q);
     }
     return fminf(a, trunc);
 }
 
-template <int C>
+template <int MODE>
 __global__ void __launch_bounds__(256) k_cost(const uint8_t *__restrict__ left, const uint8_t *__restrict__ right,
-                                             int64_t stride, int s, int wo, int ho, int L, float trunc, int rgb_mode,
+                                             int64_t stride, int s, int wo, int ho, int L, float trunc,
                                              float *__restrict__ cost)
 {
+    constexpr int C = ad_channels(MODE);
     extern __shared__ uint32_t lds[];
     uint32_t *lpx = lds;               // [kSeg]
     uint32_t *rpx = lds + kSeg;        // [kSeg + L - 1]
@@ -80,7 +90,7 @@ __global__ void __launch_bounds__(256) k_cost(const uint8_t *__restrict__ left, 
     const int64_t plane = (int64_t)wo * ho;
     float *out = cost + (int64_t)y * wo + x;
     for (int d = 0; d < L; ++d) {
-        const float v = x - d >= 0 ? ad_cost<C>(lv, rpx[tid + (L - 1) - d], rgb_mode, trunc) : trunc;
+        const float v = x - d >= 0 ? ad_cost<MODE>(lv, rpx[tid + (L - 1) - d], trunc) : trunc;
         out[(int64_t)d * plane] = v;
     }
 }
@@ -91,10 +101,11 @@ bp_status launch_cost_volume(const uint8_t *left, const uint8_t *right, int w, i
     const int wo = w / ds, ho = h / ds;
     dim3 grid((wo + kSeg - 1) / kSeg, ho);
     const size_t lds = sizeof(uint32_t) * (2 * kSeg + L - 1);
-    if (ch == 1)
-        k_cost<1><<<grid, 256, lds, s>>>(left, right, stride, ds, wo, ho, L, trunc, rgb_mode, cost);
-    else
-        k_cost<3><<<grid, 256, lds, s>>>(left, right, stride, ds, wo, ho, L, trunc, rgb_mode, cost);
+#define BP_COST(MV) k_cost<MV><<<grid, 256, lds, s>>>(left, right, stride, ds, wo, ho, L, trunc, cost)
+    if (ch == 1) BP_COST(AD_GREY);
+    else if (rgb_mode == 0) BP_COST(AD_ROUNDED);
+    else BP_COST(AD_EXACT);
+#undef BP_COST
     return launch_status();
 }
 
@@ -203,62 +214,80 @@ __global__ void __launch_bounds__(256) k_pack_pair(const uint8_t *__restrict__ l
     }
 }
 
-// One block owns row y, pixels [x0, x0 + xb) (x0 even): the packed left
-// pixels and the right pixels they can match are staged in LDS, then the
-// cost of every (pixel, label) is stored at its colour-split address
-// c * blk + label * ls + j * ps, j = y * wh + x / 2, c = (x + y) & 1.
-// Pixel-major levels (PM): consecutive lanes take consecutive labels of a
-// pixel (lp2 = L rounded up to a power of two lanes per pixel); label-major
-// levels: consecutive lanes take consecutive same-colour pixels of a label.
-template <int C, bool PM>
-__global__ void __launch_bounds__(256) k_cost_level0(const uint32_t *__restrict__ packed, int w, int h, int L,
-                                                    float trunc, int rgb_mode, int xb, int lp2, int wh, int64_t blk,
-                                                    int64_t ls, int64_t ps, float *__restrict__ out)
+// The pair as the cost kernels read it: packed words, or the frames themselves
+// when there is nothing to average (RAW).
+struct PairSrc {
+    const uint32_t *packed;           // [2][h][w]
+    const uint8_t *left, *right;
+    int64_t stride;
+};
+
+template <int C, bool RAW>
+__device__ __forceinline__ uint32_t pair_px(const PairSrc &src, int z, int x, int y, int w, int h)
+{
+    if constexpr (RAW) {
+        const uint8_t *p = (z ? src.right : src.left) + (int64_t)y * src.stride + (int64_t)x * C;
+        if constexpr (C == 1) return p[0];
+        else return (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16);
+    } else {
+        return src.packed[((int64_t)z * h + y) * w + x];
+    }
+}
+
+// Label-major levels.  One block owns row y, pixels [x0, x0 + xb) (x0 even):
+// the packed left pixels and the right pixels they can match are staged in
+// LDS, then the cost of every (pixel, label) is stored at its colour-split
+// address c * blk + label * ls + j, j = y * wh + x / 2, c = (x + y) & 1:
+// consecutive lanes take consecutive same-colour pixels of a label.
+template <int MODE>
+__global__ void __launch_bounds__(256) k_cost_level0_lm(const PairSrc src, int w, int h, int L, float trunc, int xb,
+                                                       int wh, int64_t blk, int64_t ls, float *__restrict__ out)
 {
     extern __shared__ uint32_t lds[];
+    constexpr int C = ad_channels(MODE);
     const int y = blockIdx.y, x0 = blockIdx.x * xb;
     const int nx = min(xb, w - x0);
     uint32_t *lpx = lds;             // [xb]
     uint32_t *rpx = lds + xb;        // [xb + L - 1], rpx[i] = right pixel x0 - (L - 1) + i
-    const uint32_t *lrow = packed + (int64_t)y * w;
-    const uint32_t *rrow = packed + (int64_t)w * h + (int64_t)y * w;
-    for (int i = threadIdx.x; i < nx; i += 256) lpx[i] = lrow[x0 + i];
+    for (int i = threadIdx.x; i < nx; i += 256) lpx[i] = pair_px<C, false>(src, 0, x0 + i, y, w, h);
     for (int i = threadIdx.x; i < nx + L - 1; i += 256) {
         const int x = x0 - (L - 1) + i;
-        rpx[i] = x >= 0 ? rrow[x] : 0u;
+        rpx[i] = x >= 0 ? pair_px<C, false>(src, 1, x, y, w, h) : 0u;
     }
     __syncthreads();
     // Pixels of colour 0 first, then colour 1; n0 of colour 0 in the segment.
     const int off0 = y & 1;                       // first x (relative to x0) of colour 0
     const int n0 = (nx - off0 + 1) / 2, n1 = (nx - (off0 ^ 1) + 1) / 2;
     const int np = n0 + n1;
-    auto pixel = [&](int p, int &xl, int64_t &base) {
-        const int c = p < n0 ? 0 : 1;
-        const int i = c ? p - n0 : p;
-        xl = 2 * i + (c ? off0 ^ 1 : off0);
-        const int x = x0 + xl;
-        base = (int64_t)c * blk + (int64_t)(y * wh + (x >> 1)) * ps;
-    };
-    if constexpr (PM) {
-        const int f = (int)threadIdx.x % lp2;
-        const int step = 256 / lp2;
-        if (f >= L) return;
-        for (int p = (int)threadIdx.x / lp2; p < np; p += step) {
-            int xl;
-            int64_t base;
-            pixel(p, xl, base);
-            const float v = x0 + xl - f >= 0 ? ad_cost<C>(lpx[xl], rpx[xl + (L - 1) - f], rgb_mode, trunc) : trunc;
-            out[base + (int64_t)f * ls] = v;
+    for (int f = 0; f < L; ++f)
+        for (int p = threadIdx.x; p < np; p += 256) {
+            const int c = p < n0 ? 0 : 1, i = c ? p - n0 : p;
+            const int xl = 2 * i + (c ? off0 ^ 1 : off0), x = x0 + xl;
+            const int64_t base = (int64_t)c * blk + (int64_t)y * wh + (x >> 1);
+            out[base + (int64_t)f * ls] = x - f >= 0 ? ad_cost<MODE>(lpx[xl], rpx[xl + (L - 1) - f], trunc) : trunc;
         }
-    } else {
-        for (int f = 0; f < L; ++f)
-            for (int p = threadIdx.x; p < np; p += 256) {
-                int xl;
-                int64_t base;
-                pixel(p, xl, base);
-                const float v = x0 + xl - f >= 0 ? ad_cost<C>(lpx[xl], rpx[xl + (L - 1) - f], rgb_mode, trunc) : trunc;
-                out[base + (int64_t)f * ls] = v;
-            }
+}
+
+// A block's shares of two rows of the pair in LDS: row r's left pixels
+// [x0, x0 + nx) at lds[r * (lw + span)], its right ones from x0 - (L - 1) on
+// after them (zero outside the frame).  Both rows' loads are in flight
+// together.
+template <int C, bool RAW>
+__device__ __forceinline__ void stage_rows(const PairSrc &src, uint32_t *lds, int x0, int nx, int lw, int span, int y0,
+                                           int rows, int w, int h, int L)
+{
+    const int n = nx + (nx + L - 1);
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const bool left = i < nx;
+        const int x = left ? x0 + i : x0 - (L - 1) + (i - nx);
+        uint32_t v[2] = {0u, 0u};
+        if (x >= 0) {
+            v[0] = pair_px<C, RAW>(src, left ? 0 : 1, x, y0, w, h);
+            v[1] = pair_px<C, RAW>(src, left ? 0 : 1, x, y0 + rows - 1, w, h);
+        }
+        uint32_t *at = lds + (left ? i : lw + i - nx);
+        at[0] = v[0];
+        at[lw + span] = v[1];
     }
 }
 
@@ -273,131 +302,174 @@ __global__ void __launch_bounds__(256) k_cost_level0(const uint32_t *__restrict_
 // CF: level 0's storage, FP32, FP16 (four labels in one 8-byte store) or bytes
 // (one 4-byte store); the plan chooses the narrow ones only where every value
 // is exact in them.
-template <int C, int CF>
-__global__ void __launch_bounds__(256) k_cost_level01(const uint32_t *__restrict__ packed, int w, int h, int L,
-                                                     float trunc, int rgb_mode, int xb1, int q4, int wh0,
-                                                     int64_t blk0, int64_t ps0, void *__restrict__ out0, int w1,
-                                                     int wh1, int64_t blk1, int64_t ps1, float *__restrict__ out1)
+// TWO = false: level 0 alone (out1 unused).
+// RAW: the frames need no averaging and are read here directly; the blocks
+// from nb on then initialise the messages (init_msgs_block), which the packing
+// launch does otherwise.
+// Bound by instruction issue with byte costs until the absolute differences
+// became one v_sad_u8, the two children's right pixels one run of five words
+// and the addresses 32 bits: 676 x 380 x 64 18.9 -> 11.7 us, 1352 x 760 x 128
+// 90 -> 59 us (263 MB, 4.4 TB/s), FP32 with the exact mean 127 -> 104 us (660
+// MB, 6.3 TB/s); reading the frames here saves the packing launch (160 x 120 grey
+// 3.5 us, 1352 x 760 RGB 19 us).
+template <int MODE, int CF, bool TWO, bool RAW>
+__global__ void __launch_bounds__(256) k_cost_pm(const PairSrc src, int w, int h, int L, float trunc, int gx, int nb,
+                                                int xb1, int q4, int wh0, uint32_t blk0, uint32_t ps0,
+                                                void *__restrict__ out0, int w1, int wh1, uint32_t blk1, uint32_t ps1,
+                                                float *__restrict__ out1, const InitArgs ia, int ix, int iy)
 {
     extern __shared__ uint32_t lds[];
-    const int Y = blockIdx.y, X0 = blockIdx.x * xb1;
-    const int nX = min(xb1, w1 - X0);
-    const int x0 = 2 * X0, nx = min(2 * xb1, w - x0);
-    const int span = 2 * xb1 + L - 1;
-    const int rows = min(2, h - 2 * Y);
-    // Row r of the block: lpx at lds[r * (2 xb1 + span)], rpx after it
-    // (rpx[i] = right pixel x0 - (L - 1) + i).
-    for (int r = 0; r < rows; ++r) {
-        uint32_t *lpx = lds + r * (2 * xb1 + span);
-        uint32_t *rpx = lpx + 2 * xb1;
-        const int y = 2 * Y + r;
-        const uint32_t *lrow = packed + (int64_t)y * w;
-        const uint32_t *rrow = packed + (int64_t)w * h + (int64_t)y * w;
-        for (int i = threadIdx.x; i < nx; i += 256) lpx[i] = lrow[x0 + i];
-        for (int i = threadIdx.x; i < nx + L - 1; i += 256) {
-            const int x = x0 - (L - 1) + i;
-            rpx[i] = x >= 0 ? rrow[x] : 0u;
+    constexpr int C = ad_channels(MODE);
+    if constexpr (RAW) {
+        if ((int)blockIdx.x >= nb) {
+            const int b = (int)blockIdx.x - nb, l = b / iy;
+            for (int i = b - l * iy; i < ix; i += iy) init_msgs_block(ia, i, l);
+            return;
         }
     }
+    const int Y = (int)blockIdx.x / gx, X0 = ((int)blockIdx.x - Y * gx) * xb1;
+    const int nX = min(xb1, w1 - X0);
+    const int x0 = 2 * X0, nx = min(2 * xb1, w - x0);
+    const int lw = 2 * xb1, span = lw + L - 1;
+    const int rows = min(2, h - 2 * Y);
+    stage_rows<C, RAW>(src, lds, x0, nx, lw, span, 2 * Y, rows, w, h, L);
     __syncthreads();
     const int q = (int)threadIdx.x % q4;
     const int f0 = 4 * q;
     if (f0 >= L) return;
     const int step = 256 / q4;
     for (int X = (int)threadIdx.x / q4; X < nX; X += step) {
-        float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
+        for (int jj = 0; jj < 2; ++jj) {
+            if (jj >= rows) continue;
+            const uint32_t *lpx = lds + jj * (lw + span) + 2 * X;
+            // Right pixels of the row's two children's labels f0 + 3 .. f0 and
+            // one on; those of labels past L lie before rpx, in lpx, and are
+            // not used.
+            uint32_t rv[5];
+#pragma unroll
+            for (int e = 0; e < 5; ++e) rv[e] = lpx[lw + (L - 1) - f0 - 3 + e];
 #pragma unroll
             for (int ii = 0; ii < 2; ++ii) {
-                const int xl = 2 * X + ii, x = x0 + xl, y = 2 * Y + jj;
-                if (xl >= nx || jj >= rows) continue;
-                const uint32_t *lpx = lds + jj * (2 * xb1 + span);
-                const uint32_t *rpx = lpx + 2 * xb1;
-                const uint32_t lv = lpx[xl];
+                const int x = x0 + 2 * X + ii, y = 2 * Y + jj;
+                if (x >= w) continue;
+                const uint32_t lv = lpx[ii];
+                const int nf = min(L, x + 1) - f0;              // labels with a match from f0 on
                 float v[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int f = f0 + e;
-                    v[e] = (f < L && x - f >= 0) ? ad_cost<C>(lv, rpx[xl + (L - 1) - f], rgb_mode, trunc) : trunc;
+                    const float a = ad_cost<MODE>(lv, rv[3 - e + ii], trunc);
+                    v[e] = e < nf ? a : trunc;
+                    acc[e] += v[e];
                 }
-                const int64_t e0 = (int64_t)((x + y) & 1) * blk0 + (int64_t)(y * wh0 + (x >> 1)) * ps0 + f0;
+                const uint32_t e0 = (uint32_t)((x + y) & 1) * blk0 + (uint32_t)(y * wh0 + (x >> 1)) * ps0 + (uint32_t)f0;
                 if constexpr (CF == COST_F16) {
                     typedef _Float16 h4_t __attribute__((ext_vector_type(4)));
                     const h4_t hv = {(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
                     *(h4_t *)((_Float16 *)out0 + e0) = hv;
                 } else if constexpr (CF == COST_U8) {
-                    *(uint32_t *)((uint8_t *)out0 + e0) = (uint32_t)v[0] | ((uint32_t)v[1] << 8) |
-                                                          ((uint32_t)v[2] << 16) | ((uint32_t)v[3] << 24);
+                    uint32_t p = 0u;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) p = __builtin_amdgcn_cvt_pk_u8_f32(v[e], (uint32_t)e, p);
+                    *(uint32_t *)((uint8_t *)out0 + e0) = p;
                 } else {
                     *(float4 *)((float *)out0 + e0) = make_float4(v[0], v[1], v[2], v[3]);
                 }
-                acc.x += v[0];
-                acc.y += v[1];
-                acc.z += v[2];
-                acc.w += v[3];
             }
-        const int Xg = X0 + X;
-        *(float4 *)(out1 + (int64_t)((Xg + Y) & 1) * blk1 + (int64_t)(Y * wh1 + (Xg >> 1)) * ps1 + f0) = acc;
+        }
+        if constexpr (TWO) {
+            const int Xg = X0 + X;
+            *(float4 *)(out1 + (uint32_t)((Xg + Y) & 1) * blk1 + (uint32_t)(Y * wh1 + (Xg >> 1)) * ps1 + (uint32_t)f0) =
+                make_float4(acc[0], acc[1], acc[2], acc[3]);
+        }
     }
+}
+
+template <int MODE, int CF>
+static void launch_cost_pm(const PairSrc &src, bool raw, const Plan &p, float trunc, uint8_t *ws, const InitArgs &ia,
+                           unsigned ix, hipStream_t st)
+{
+    const Level &v = p.lv[0];
+    const bool two = p.levels >= 2;
+    const Level &v1 = p.lv[two ? 1 : 0];
+    const int L = p.L;
+    // 16-byte stores need every pixel's row (lp labels) to be a multiple of 4.
+    int q4 = 1;
+    while (4 * q4 < L) q4 <<= 1;
+    const int w1 = (v.w + 1) / 2, h1 = (v.h + 1) / 2;
+    // Level-1 pixels per block: each block stages L - 1 right pixels on top of its
+    // own, more of them with more labels.  16 / 32 / 64: 676 x 380 x 64 bytes 12.0
+    // / 11.7 / 12.3 us, 1352 x 760 x 128 bytes 71.6 / 65.7 / 59.6, FP32 118 / 104
+    // / 104.
+    const int xb1 = q4 > 16 ? 64 : 32;
+    const int gx = (w1 + xb1 - 1) / xb1, nb = gx * h1;
+    const int iy = (int)std::min(ix, 256u);   // initialisation blocks per level
+    const unsigned grid = (unsigned)nb + (raw ? (unsigned)(iy * (p.levels + 1)) : 0u);
+    const size_t lds = sizeof(uint32_t) * (size_t)2 * (4 * xb1 + L - 1);
+    void *out0 = ws + v.cost_off;
+    float *out1 = two ? (float *)(ws + v1.cost_off) : nullptr;
+#define BP_COST_PM(TV, RV)                                                                                        \
+    k_cost_pm<MODE, CF, TV, RV><<<grid, 256, lds, st>>>(src, v.w, v.h, L, trunc, gx, nb, xb1, q4, v.wh,           \
+                                                        (uint32_t)v.blk, (uint32_t)v.ps, out0, w1, v1.wh,         \
+                                                        (uint32_t)v1.blk, (uint32_t)v1.ps, out1, ia, (int)ix, iy)
+    if (two) {
+        if (raw) BP_COST_PM(true, true);
+        else BP_COST_PM(true, false);
+    } else {
+        if (raw) BP_COST_PM(false, true);
+        else BP_COST_PM(false, false);
+    }
+#undef BP_COST_PM
 }
 
 bp_status launch_pair_cost(const bp_pair &pr, const Plan &p, uint8_t *ws, hipStream_t st, int *levels_done)
 {
-    // The message initialisation runs in the packing's launch.
     const Level &v = p.lv[0];
     const int w = v.w, h = v.h, L = p.L;
     uint32_t *packed = (uint32_t *)(ws + p.pair_off);
-    const int gx = (w + 255) / 256, gy = h < 4096 ? h : 4096;
+    const int mode = pr.channels == 1 ? AD_GREY : pr.rgb_mode == 0 ? AD_ROUNDED : AD_EXACT;
+    const bool pm = v.layout == PIXEL_MAJOR && (p.levels < 2 || p.lv[1].layout == PIXEL_MAJOR);
+    // Nothing to average: the cost kernel reads the frames.
+    const bool raw = pm && pr.downsample == 1;
+    const PairSrc src{packed, pr.left, pr.right, pr.row_stride_bytes};
     unsigned ix;
     const InitArgs ia = init_args(p, ws, &ix);
-    const unsigned g1 = (unsigned)(gx * gy * 2) + ix * (unsigned)(p.levels + 1);
-    // Word loads when every pixel block's row chunk is word-aligned.
-    const bool words = pr.downsample % 4 == 0 && pr.row_stride_bytes % 4 == 0 && ((uintptr_t)pr.left % 4) == 0 &&
-                       ((uintptr_t)pr.right % 4) == 0;
+    if (!raw) {
+        // The message initialisation runs in the packing's launch.
+        const int gx = (w + 255) / 256, gy = h < 4096 ? h : 4096;
+        const unsigned g1 = (unsigned)(gx * gy * 2) + ix * (unsigned)(p.levels + 1);
+        // Word loads when every pixel block's row chunk is word-aligned.
+        const bool words = pr.downsample % 4 == 0 && pr.row_stride_bytes % 4 == 0 && ((uintptr_t)pr.left % 4) == 0 &&
+                           ((uintptr_t)pr.right % 4) == 0;
 #define BP_PACK_S(CV, WV, SV) \
     k_pack_pair<CV, WV, SV><<<g1, 256, 0, st>>>(pr.left, pr.right, pr.row_stride_bytes, pr.downsample, w, h, packed, \
                                                 gx, gy, ia, (int)ix)
 #define BP_PACK(CV, WV) BP_PACK_S(CV, WV, 0)
-    if (pr.channels == 1) {
-        if (words) BP_PACK(1, true);
-        else BP_PACK(1, false);
-    } else {
-        if (words && pr.downsample == 4) BP_PACK_S(3, true, 4);
-        else if (words) BP_PACK(3, true);
-        else BP_PACK(3, false);
-    }
+        if (pr.channels == 1) {
+            if (words) BP_PACK(1, true);
+            else BP_PACK(1, false);
+        } else {
+            if (words && pr.downsample == 4) BP_PACK_S(3, true, 4);
+            else if (words) BP_PACK(3, true);
+            else BP_PACK(3, false);
+        }
 #undef BP_PACK_S
 #undef BP_PACK
-    int lp2 = 1;
-    while (lp2 < L) lp2 <<= 1;
-    if (p.levels >= 2 && v.layout == PIXEL_MAJOR && p.lv[1].layout == PIXEL_MAJOR) {
-        const Level &v1 = p.lv[1];
-        // 16-byte stores need every pixel's row (lp labels) to be a multiple of 4.
-        int q4 = 1;
-        while (4 * q4 < L) q4 <<= 1;
-        const int xb1 = 16;   // 16: 19.0 us at 676x380x64, against 19.9 (32) and 20.5 (64)
-        const dim3 grid1((unsigned)((v1.w + xb1 - 1) / xb1), (unsigned)v1.h);
-        const size_t lds1 = sizeof(uint32_t) * (size_t)2 * (2 * xb1 + 2 * xb1 + L - 1);
-        void *out0 = ws + v.cost_off;
-        float *out1 = (float *)(ws + v1.cost_off);
-#define BP_COST01(CV, HV)                                                                                   \
-    k_cost_level01<CV, HV><<<grid1, 256, lds1, st>>>(packed, w, h, L, pr.data_trunc, pr.rgb_mode, xb1, q4, v.wh, \
-                                                     v.blk, v.ps, out0, v1.w, v1.wh, v1.blk, v1.ps, out1)
-        if (pr.channels == 1) {
-            if (v.cost_fmt == COST_F16) BP_COST01(1, COST_F16);
-            else if (v.cost_fmt == COST_U8) BP_COST01(1, COST_U8);
-            else BP_COST01(1, COST_F32);
-        } else {
-            if (v.cost_fmt == COST_F16) BP_COST01(3, COST_F16);
-            else if (v.cost_fmt == COST_U8) BP_COST01(3, COST_U8);
-            else BP_COST01(3, COST_F32);
-        }
-#undef BP_COST01
-        *levels_done = 2;
-        return launch_status();
     }
     *levels_done = 1;
+    if (pm) {
+#define BP_COST_CF(CFV)                                                                                          \
+    if (mode == AD_GREY) launch_cost_pm<AD_GREY, CFV>(src, raw, p, pr.data_trunc, ws, ia, ix, st);               \
+    else if (mode == AD_ROUNDED) launch_cost_pm<AD_ROUNDED, CFV>(src, raw, p, pr.data_trunc, ws, ia, ix, st);    \
+    else launch_cost_pm<AD_EXACT, CFV>(src, raw, p, pr.data_trunc, ws, ia, ix, st);
+        if (v.cost_fmt == COST_F16) { BP_COST_CF(COST_F16) }
+        else if (v.cost_fmt == COST_U8) { BP_COST_CF(COST_U8) }
+        else { BP_COST_CF(COST_F32) }
+#undef BP_COST_CF
+        if (p.levels >= 2) *levels_done = 2;
+        return launch_status();
+    }
     // Row segments of at most 256 pixels, balanced, even width.
     const int nseg = (w + 255) / 256;
     int xb = (w + nseg - 1) / nseg;
@@ -405,17 +477,11 @@ bp_status launch_pair_cost(const bp_pair &pr, const Plan &p, uint8_t *ws, hipStr
     const dim3 grid((unsigned)((w + xb - 1) / xb), (unsigned)h);
     const size_t lds = sizeof(uint32_t) * (size_t)(2 * xb + L - 1);
     float *out = (float *)(ws + v.cost_off);
-    const bool pm = v.layout == PIXEL_MAJOR;
-#define BP_COST0(CV, PMV)                                                                                    \
-    k_cost_level0<CV, PMV><<<grid, 256, lds, st>>>(packed, w, h, L, pr.data_trunc, pr.rgb_mode, xb, lp2, v.wh, \
-                                                   v.blk, v.ls, v.ps, out)
-    if (pr.channels == 1) {
-        if (pm) BP_COST0(1, true);
-        else BP_COST0(1, false);
-    } else {
-        if (pm) BP_COST0(3, true);
-        else BP_COST0(3, false);
-    }
+#define BP_COST0(MV) \
+    k_cost_level0_lm<MV><<<grid, 256, lds, st>>>(src, w, h, L, pr.data_trunc, xb, v.wh, v.blk, v.ls, out)
+    if (mode == AD_GREY) BP_COST0(AD_GREY);
+    else if (mode == AD_ROUNDED) BP_COST0(AD_ROUNDED);
+    else BP_COST0(AD_EXACT);
 #undef BP_COST0
     return launch_status();
 }
