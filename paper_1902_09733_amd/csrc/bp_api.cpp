@@ -414,13 +414,11 @@ bp_status run_one(const bp_problem &q, const Plan &pl, const bp_params &p, uint8
                               sb, s)) != BP_OK)
             return st;
     }
-    if ((q.disparity || q.soft_disparity) && !ro_all) {
-        // After the fused readout only the last receivers' labels remain.
-        const int mask = fuse_ro ? (1 << (K & 1)) : 3;
-        if ((st = launch_readout(pl, mask, q.disparity, q.soft_disparity, p.temperature, ws, s)) != BP_OK) return st;
-    }
-    if (q.messages_out)
-        if ((st = launch_export(pl, q.messages_out, ws, s)) != BP_OK) return st;
+    // After the fused readout only the last receivers' labels remain.
+    const int mask = fuse_ro ? (1 << (K & 1)) : 3;
+    if (q.messages_out) return launch_export(pl, q.messages_out, ws, s, mask, q.disparity, q.soft_disparity, p.temperature);
+    if ((q.disparity || q.soft_disparity) && !ro_all)
+        return launch_readout(pl, mask, q.disparity, q.soft_disparity, p.temperature, ws, s);
     return BP_OK;
 }
 
@@ -526,11 +524,11 @@ bp_status finish_batched(const bp_problem *probs, int32_t count, const Plan *pla
     for (int i = 0; i < count && st == BP_OK; ++i) {
         if (in_group && in_group[i] != g) continue;
         const bp_problem &q = probs[i];
-        if ((q.disparity || q.soft_disparity) && !(read_out && read_out[i])) {
-            const int mask = fuse[i] ? (1 << (K & 1)) : 3;
+        const int mask = fuse[i] ? (1 << (K & 1)) : 3;
+        if (q.messages_out)
+            st = launch_export(plans[i], q.messages_out, ws, s, mask, q.disparity, q.soft_disparity, p.temperature);
+        else if ((q.disparity || q.soft_disparity) && !(read_out && read_out[i]))
             st = launch_readout(plans[i], mask, q.disparity, q.soft_disparity, p.temperature, ws, s);
-        }
-        if (st == BP_OK && q.messages_out) st = launch_export(plans[i], q.messages_out, ws, s);
     }
     return st;
 }

@@ -748,60 +748,117 @@ __global__ void __launch_bounds__(256) k_export(const uint8_t *__restrict__ msg,
     out[(((int64_t)k * L + f) * d.h + y) * d.w + x] = v;
 }
 
-// Pixel-major level 0: through an LDS tile of 32 consecutive pixels of one
-// row (their slot-k rows read as contiguous runs, labels written as 128-byte
-// runs of x; rows padded by one word).  grid (ceil(w / 32), h, 4).
-template <typename S, int LP>
-__global__ void __launch_bounds__(256) k_export_pm(const uint8_t *__restrict__ msg, uint32_t msg_bytes, LevelDesc d,
-                                                  int L, float *__restrict__ out)
+// Pixel-major level 0: through an LDS tile of TP consecutive pixels of one
+// row, SEG lanes (R labels each) loading a pixel's rows of all four slots in
+// vectors, labels written as runs of x (rows padded by one word).  READ: the
+// same rows give the pixels of the colours in `mask` their beliefs, read out as
+// in k_readout_pm.  grid (ceil(w / TP), h).
+// Memory bound.  333 x 187 x 48 (64 stored) in FP32, 128 MB: 25 us with the
+// readout, against 25 and 13 us as two passes over the rows.
+template <int SEG, int R, typename S, int CF, bool READ>
+__global__ void __launch_bounds__(256) k_export_pm(const float *__restrict__ cost, uint32_t cost_bytes,
+                                                  const uint8_t *__restrict__ msg, uint32_t msg_bytes, LevelDesc d,
+                                                  int L, float *__restrict__ out, int mask, int32_t *__restrict__ disp,
+                                                  float *__restrict__ soft, float inv_t)
 {
-    __shared__ float tile[32][LP + 1];
-    const int x0 = blockIdx.x * 32, y = blockIdx.y, k = blockIdx.z;
-    const __amdgpu_buffer_rsrc_t r = make_rsrc(msg, msg_bytes);
-    for (int e = threadIdx.x; e < 32 * LP; e += 256) {
-        const int p = e / LP, f = e - p * LP;
-        const int x = x0 + p;
-        if (x >= d.w) continue;
-        const bool ok = (k == 0) ? x > 0 : (k == 1) ? x < d.w - 1 : (k == 2) ? y > 0 : y < d.h - 1;
-        float v = 0.0f;
-        if (ok) {
-            const int64_t idx = msg_idx((x + y) & 1, k, f, y * d.wh + (x >> 1), d.blk, d.ls, d.ps);
-            v = S::ld(r, (uint32_t)(idx * S::bytes), 0);
-        }
-        tile[p][f] = v;
+    constexpr int LP = SEG * R, TP = LP <= 64 ? 64 : 32, PPB = 256 / SEG, PASSES = TP / PPB;
+    __shared__ float tile[TP][LP + 1];
+    const int x0 = blockIdx.x * TP, y = blockIdx.y;
+    const __amdgpu_buffer_rsrc_t rc = make_rsrc(cost, cost_bytes);
+    const __amdgpu_buffer_rsrc_t rm = make_rsrc(msg, msg_bytes);
+    const int s = (int)threadIdx.x % SEG, p0 = (int)threadIdx.x / SEG, f0 = s * R;
+    float m[PASSES][4][R], b[PASSES][R];
+#pragma unroll
+    for (int q = 0; q < PASSES; ++q) {
+        const int x = min(x0 + q * PPB + p0, d.w - 1), c = (x + y) & 1;
+        const uint32_t base = (uint32_t)(y * d.wh + (x >> 1)) * (uint32_t)LP + (uint32_t)f0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) ld_row<S, R>(rm, ((uint32_t)((c * 4 + k) * d.blk) + base) * S::bytes, m[q][k]);
+        if constexpr (READ) ld_cost<R, CF>(rc, (uint32_t)(c * d.blk) + base, b[q]);
     }
-    __syncthreads();
-    for (int e = threadIdx.x; e < 32 * L; e += 256) {
-        const int f = e / 32, p = e - f * 32;
-        const int x = x0 + p;
-        if (x < d.w) out[(((int64_t)k * L + f) * d.h + y) * d.w + x] = tile[p][f];
+    if constexpr (READ) {
+#pragma unroll
+        for (int q = 0; q < PASSES; ++q) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int r = 0; r < R; ++r) b[q][r] += m[q][k][r];
+            int bi;
+            float sv;
+            pm_readout<SEG, R, false>(b[q], f0, L, soft != nullptr, inv_t, bi, sv);
+            const int x = x0 + q * PPB + p0;
+            if (s == 0 && x < d.w && ((mask >> ((x + y) & 1)) & 1)) {
+                const int64_t o = (int64_t)y * d.w + x;
+                if (soft) soft[o] = sv;
+                if (disp) disp[o] = bi;
+            }
+        }
+    }
+    const int tp = (int)threadIdx.x % TP, tx = x0 + tp;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (k) __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PASSES; ++q) {
+            const int p = q * PPB + p0, x = x0 + p;
+            // Slots from outside the grid are zero.
+            const bool ok = (k == 0) ? x > 0 : (k == 1) ? x < d.w - 1 : (k == 2) ? y > 0 : y < d.h - 1;
+#pragma unroll
+            for (int r = 0; r < R; ++r) tile[p][f0 + r] = ok ? m[q][k][r] : 0.0f;
+        }
+        __syncthreads();
+        if (tx < d.w)
+            for (int f = (int)threadIdx.x / TP; f < L; f += 256 / TP)
+                out[(((int64_t)k * L + f) * d.h + y) * d.w + tx] = tile[tp][f];
     }
 }
 
-bp_status launch_export(const Plan &p, float *out, uint8_t *ws, hipStream_t s)
+bp_status launch_export(const Plan &p, float *out, uint8_t *ws, hipStream_t s, int colour_mask, int32_t *disp,
+                        float *soft, float temperature)
 {
     const Level &v = p.lv[0];
+    const bool read = colour_mask != 0 && (disp || soft);
+    if (v.layout != PIXEL_MAJOR) {
+        if (read) {
+            const bp_status st = launch_readout(p, colour_mask, disp, soft, temperature, ws, s);
+            if (st != BP_OK) return st;
+        }
+        return with_store(v.fmt, [&](auto st) {
+            k_export<decltype(st)><<<dim3(cdiv(v.w, 256), v.h, 4 * p.L), 256, 0, s>>>(
+                ws + v.msg_off, (uint32_t)v.msg_bytes, desc(v), p.L, out);
+            return launch_status();
+        });
+    }
+    const float inv_t = soft ? 1.0f / temperature : 0.0f;
+    int SEGV, RV;
+    pm_split(p.L, &SEGV, &RV);
     return with_store(v.fmt, [&](auto st) {
         using S = decltype(st);
-        if (v.layout == PIXEL_MAJOR) {
-            const dim3 grid(cdiv(v.w, 32), v.h, 4);
-            const uint8_t *m = ws + v.msg_off;
-            const uint32_t mb = (uint32_t)v.msg_bytes;
-            switch (v.lp) {
-            case 16: k_export_pm<S, 16><<<grid, 256, 0, s>>>(m, mb, desc(v), p.L, out); break;
-            case 32: k_export_pm<S, 32><<<grid, 256, 0, s>>>(m, mb, desc(v), p.L, out); break;
-            case 64: k_export_pm<S, 64><<<grid, 256, 0, s>>>(m, mb, desc(v), p.L, out); break;
-            case 96: k_export_pm<S, 96><<<grid, 256, 0, s>>>(m, mb, desc(v), p.L, out); break;
-            case 128: k_export_pm<S, 128><<<grid, 256, 0, s>>>(m, mb, desc(v), p.L, out); break;
-            case 192: k_export_pm<S, 192><<<grid, 256, 0, s>>>(m, mb, desc(v), p.L, out); break;
-            case 256: k_export_pm<S, 256><<<grid, 256, 0, s>>>(m, mb, desc(v), p.L, out); break;
-            default: return BP_ERR_UNSUPPORTED;
-            }
-            return launch_status();
-        }
-        k_export<S><<<dim3(cdiv(v.w, 256), v.h, 4 * p.L), 256, 0, s>>>(ws + v.msg_off, (uint32_t)v.msg_bytes, desc(v),
-                                                                        p.L, out);
-        return launch_status();
+        const float *cost = (const float *)(ws + v.cost_off);
+#define BP_EX_LAUNCH(SV, R, CFV, RD)                                                                           \
+    k_export_pm<SV, R, S, CFV, RD><<<dim3(cdiv(v.w, SV * R <= 64 ? 64 : 32), v.h), 256, 0, s>>>(               \
+        cost, (uint32_t)v.cost_bytes, ws + v.msg_off, (uint32_t)v.msg_bytes, desc(v), p.L, out, colour_mask,   \
+        disp, soft, inv_t)
+#define BP_EX_CASE(SV, R)                                                                                       \
+    if (SEGV == SV && RV == R) {                                                                                \
+        if (!read) BP_EX_LAUNCH(SV, R, COST_F32, false);                                                        \
+        else if (v.cost_fmt == COST_F16) BP_EX_LAUNCH(SV, R, COST_F16, true);                                   \
+        else if (v.cost_fmt == COST_U8) {                                                                       \
+            if constexpr (R % 4 == 0) BP_EX_LAUNCH(SV, R, COST_U8, true);                                       \
+            else return BP_ERR_UNSUPPORTED;                                                                     \
+        } else BP_EX_LAUNCH(SV, R, COST_F32, true);                                                             \
+        return launch_status();                                                                                 \
+    }
+        BP_EX_CASE(4, 4)
+        BP_EX_CASE(8, 4)
+        BP_EX_CASE(16, 4)
+        BP_EX_CASE(16, 6)
+        BP_EX_CASE(16, 8)
+        BP_EX_CASE(16, 12)
+        BP_EX_CASE(16, 16)
+#undef BP_EX_CASE
+#undef BP_EX_LAUNCH
+        return BP_ERR_UNSUPPORTED;
     });
 }
 

@@ -141,7 +141,10 @@ bp_status launch_iteration_from(const Plan &p, int t, const uint8_t *src, float 
 // a6: readout of the pixels of `colour_mask` (bit c = colour c) at level 0.
 bp_status launch_readout(const Plan &p, int colour_mask, int32_t *disp, float *soft, float temperature,
                          uint8_t *ws, hipStream_t s);
-bp_status launch_export(const Plan &p, float *out, uint8_t *ws, hipStream_t s);
+// The final messages as planar float32 [4][L][h][w], and the same readout in
+// the same pass (colour_mask 0: none).
+bp_status launch_export(const Plan &p, float *out, uint8_t *ws, hipStream_t s, int colour_mask, int32_t *disp,
+                        float *soft, float temperature);
 
 // Measurement aid: stream read_bytes from src and write_bytes to dst.
 bp_status launch_stream(const void *src, size_t read_bytes, void *dst, size_t write_bytes, hipStream_t s);
