@@ -100,35 +100,26 @@ __global__ void __launch_bounds__(256) k_split_lm(const float *__restrict__ plan
     out[cost_idx((x + y) & 1, f, y * d.wh + (x >> 1), d.blk, d.ls, d.ps)] = v;
 }
 
-// Cost of one pixel and label at a label-major or planar source level, summed
-// over the (up to four) children when SUM (pyramid step), in the order
-// (0,0), (1,0), (0,1), (1,1).
-template <bool FROM_PLANAR, bool SUM>
+// Cost of one pixel and label of a pyramid step: the sum over the (up to four)
+// children at a label-major source level, in the order (0,0), (1,0), (0,1),
+// (1,1).
 __device__ __forceinline__ float gather_cost(const float *__restrict__ src, const LevelDesc &s, int f, int x, int y)
 {
-    auto at = [&](int fx, int fy) -> float {
-        if constexpr (FROM_PLANAR) return src[((int64_t)f * s.h + fy) * s.w + fx];
-        else return src[cost_idx((fx + fy) & 1, f, fy * s.wh + (fx >> 1), s.blk, s.ls, s.ps)];
-    };
-    if constexpr (!SUM) {
-        return at(x, y);
-    } else {
-        float acc = 0.0f;
+    float acc = 0.0f;
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
+    for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-            for (int ii = 0; ii < 2; ++ii) {
-                const int fx = 2 * x + ii, fy = 2 * y + jj;
-                if (fx < s.w && fy < s.h) acc += at(fx, fy);
-            }
-        return acc;
-    }
+        for (int ii = 0; ii < 2; ++ii) {
+            const int fx = 2 * x + ii, fy = 2 * y + jj;
+            if (fx < s.w && fy < s.h)
+                acc += src[cost_idx((fx + fy) & 1, f, fy * s.wh + (fx >> 1), s.blk, s.ls, s.ps)];
+        }
+    return acc;
 }
 
 // Transposing tile: 64 pixels of one row x 32 labels, read along the row from a
-// planar or label-major source and written along the labels into a
-// pixel-major level.  grid (w_out/64, h_out, L/32).
-template <bool FROM_PLANAR, bool SUM>
+// label-major source's sums and written along the labels into a pixel-major
+// level.  grid (w_out/64, h_out, L/32).
 __global__ void __launch_bounds__(256) k_to_pm(const float *__restrict__ src, LevelDesc s, float *__restrict__ out,
                                               LevelDesc d, int L)
 {
@@ -138,7 +129,7 @@ __global__ void __launch_bounds__(256) k_to_pm(const float *__restrict__ src, Le
         const int fl = i / 64, xl = i % 64;
         const int x = x0 + xl, f = f0 + fl;
         float v = 0.0f;
-        if (x < d.w && f < L) v = gather_cost<FROM_PLANAR, SUM>(src, s, f, x, y);
+        if (x < d.w && f < L) v = gather_cost(src, s, f, x, y);
         tile[fl][xl] = v;
     }
     __syncthreads();
@@ -153,9 +144,12 @@ __global__ void __launch_bounds__(256) k_to_pm(const float *__restrict__ src, Le
 // a block moves 64 pixels of one row x 64 labels through LDS, loading four
 // consecutive pixels of one label per lane (256-byte runs along the row) and
 // storing four consecutive labels of one pixel per lane (a pixel's labels
-// are contiguous).  Needs w % 4 == 0 and a 16-byte aligned source; labels
+// are contiguous).  ALIGNED: w % 4 == 0 and a 16-byte aligned source; else the
+// loads are 4-byte aligned and a row's last pixels come one by one.  Labels
 // from L up to the next multiple of four are stored as zero (they lie inside
-// the pixel's padded row, lp being a multiple of four).  grid (w/64, h, L/64).
+// the pixel's padded row, lp being a multiple of four).  Memory bound; 333 x
+// 187 x 48, unaligned: 6.9 us against 9.5 with 4-byte accesses.  grid (w/64, h, L/64).
+template <bool ALIGNED>
 __global__ void __launch_bounds__(256) k_split_pm4(const float *__restrict__ src, float *__restrict__ out,
                                                   LevelDesc d, int L)
 {
@@ -166,7 +160,16 @@ __global__ void __launch_bounds__(256) k_split_pm4(const float *__restrict__ src
     for (int i = 0; i < 4; ++i) {
         const int fl = r + 16 * i, f = f0 + fl, x = x0 + 4 * q;
         float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (f < L && x < d.w) v = *(const float4 *)(src + ((int64_t)f * d.h + y) * d.w + x);
+        const float *p = src + ((int64_t)f * d.h + y) * d.w + x;
+        if constexpr (ALIGNED) {
+            if (f < L && x < d.w) v = *(const float4 *)p;
+        } else if (f < L && x + 3 < d.w) {
+            __builtin_memcpy(&v, p, 16);
+        } else if (f < L && x < d.w) {
+            v.x = p[0];
+            if (x + 1 < d.w) v.y = p[1];
+            if (x + 2 < d.w) v.z = p[2];
+        }
         tile[fl][4 * q] = v.x;
         tile[fl][4 * q + 1] = v.y;
         tile[fl][4 * q + 2] = v.z;
@@ -190,7 +193,7 @@ __global__ void __launch_bounds__(256) k_pyr_lm(const float *__restrict__ fine, 
 {
     const int x = blockIdx.x * 256 + threadIdx.x, y = blockIdx.y, f = blockIdx.z;
     if (x >= d.w) return;
-    out[cost_idx((x + y) & 1, f, y * d.wh + (x >> 1), d.blk, d.ls, d.ps)] = gather_cost<false, true>(fine, s, f, x, y);
+    out[cost_idx((x + y) & 1, f, y * d.wh + (x >> 1), d.blk, d.ls, d.ps)] = gather_cost(fine, s, f, x, y);
 }
 
 // pixel-major -> pixel-major pyramid step: threads along (pixel, label) with
@@ -217,11 +220,10 @@ bp_status launch_split_cost(const float *planar, const Plan &p, uint8_t *ws, hip
     const Level &v = p.lv[0];
     float *out = (float *)(ws + v.cost_off);
     LevelDesc d = desc(v);
-    if (v.layout == PIXEL_MAJOR && v.w % 4 == 0 && ((uintptr_t)planar % 16) == 0) {
-        k_split_pm4<<<dim3(cdiv(v.w, 64), v.h, cdiv(p.L, 64)), 256, 0, s>>>(planar, out, d, p.L);
-    } else if (v.layout == PIXEL_MAJOR) {
-        LevelDesc src{v.w, v.h, 0, 0, 0, 0};
-        k_to_pm<true, false><<<dim3(cdiv(v.w, 64), v.h, cdiv(p.L, 32)), 256, 0, s>>>(planar, src, out, d, p.L);
+    if (v.layout == PIXEL_MAJOR) {
+        const dim3 grid(cdiv(v.w, 64), v.h, cdiv(p.L, 64));
+        if (v.w % 4 == 0 && ((uintptr_t)planar % 16) == 0) k_split_pm4<true><<<grid, 256, 0, s>>>(planar, out, d, p.L);
+        else k_split_pm4<false><<<grid, 256, 0, s>>>(planar, out, d, p.L);
     } else {
         k_split_lm<<<dim3(cdiv(v.w, 256), v.h, p.L), 256, 0, s>>>(planar, out, d);
     }
@@ -332,7 +334,7 @@ bp_status launch_pyramid_level(const Plan &p, int l, uint8_t *ws, hipStream_t s)
     if (c.layout == LABEL_MAJOR) {
         k_pyr_lm<<<dim3(cdiv(c.w, 256), c.h, p.L), 256, 0, s>>>(fine, desc(f), out, desc(c));
     } else if (f.layout == LABEL_MAJOR) {
-        k_to_pm<false, true><<<dim3(cdiv(c.w, 64), c.h, cdiv(p.L, 32)), 256, 0, s>>>(fine, desc(f), out, desc(c), p.L);
+        k_to_pm<<<dim3(cdiv(c.w, 64), c.h, cdiv(p.L, 32)), 256, 0, s>>>(fine, desc(f), out, desc(c), p.L);
     } else {
         k_pyr_pm<<<dim3(cdiv((int64_t)c.w * p.L, 256), c.h), 256, 0, s>>>(fine, desc(f), out, desc(c), p.L);
     }
