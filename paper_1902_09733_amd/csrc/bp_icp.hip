@@ -738,18 +738,23 @@ __global__ void k_copy_f64(const double *__restrict__ src, double *__restrict__ 
     if (k < n) dst[k] = src[k];
 }
 
-static uint32_t icp_buckets(int m)
+// Buckets of both clouds' tables: a power of two, two per point of the larger
+// cloud while that fits 32 bits (never fewer buckets than points).
+static uint32_t icp_buckets(int n, int m)
 {
+    const uint64_t want = 2 * (uint64_t)std::max(n, m);
     uint32_t T = 1024;
-    while (T < 2u * (uint32_t)m) T <<= 1;
+    while (T < want && T < (1u << 31)) T <<= 1;
     return T;
 }
 
+static int blocks_of(int n, int per) { return (int)(((int64_t)n + per - 1) / per); }
+
 size_t icp_workspace_bytes(int n, int m)
 {
-    const uint32_t T = icp_buckets(n > m ? n : m);
-    const size_t nb = (size_t)((n + kIcpBlock - 1) / kIcpBlock);
-    return 2 * (align_up((size_t)(T + 1) * 4) * 2 + align_up((size_t)(T / 1024) * 4)) + align_up((size_t)m * 16) +
+    const uint32_t T = icp_buckets(n, m);
+    const size_t nb = (size_t)blocks_of(n, kIcpBlock);
+    return 2 * (align_up(((size_t)T + 1) * 4) * 2 + align_up((size_t)(T / 1024) * 4)) + align_up((size_t)m * 16) +
            2 * align_up((size_t)n * 16) +
            align_up(nb * kIcpSums * 8 + 8) + align_up(12 * 8) + align_up(12 * 4) + align_up(kBoxBlocks * 6 * 4) +
            align_up(sizeof(IcpHash)) + align_up((size_t)n * 4) + align_up((size_t)m * 4);
@@ -758,15 +763,15 @@ size_t icp_workspace_bytes(int n, int m)
 bp_status launch_icp(const float *src, int n, const float *dst, int m, const double *pose_in, int iters, float dmax,
                      double *pose_out, double *rms, int32_t *pairs, int32_t *corr_out, uint8_t *ws, hipStream_t st)
 {
-    const uint32_t T = icp_buckets(n > m ? n : m);
-    const int nb = (n + kIcpBlock - 1) / kIcpBlock;
+    const uint32_t T = icp_buckets(n, m);
+    const int nb = blocks_of(n, kIcpBlock);
     uint8_t *p = ws;
     IcpSorts so;
     for (IcpSort &c : so.c) {
         c.count = (uint32_t *)p;
-        p += align_up((size_t)(T + 1) * 4);
+        p += align_up(((size_t)T + 1) * 4);
         c.start = (uint32_t *)p;
-        p += align_up((size_t)(T + 1) * 4);
+        p += align_up(((size_t)T + 1) * 4);
         c.tile = (uint32_t *)p;
         p += align_up((size_t)(T / 1024) * 4);
     }
@@ -802,8 +807,8 @@ bp_status launch_icp(const float *src, int n, const float *dst, int m, const dou
     so.c[1].rank = rank_dst;
     uint32_t log2T = 0;
     while ((1u << log2T) < T) ++log2T;
-    const int nparts = m > 0 ? std::min(kBoxBlocks, (m + 255) / 256) : 0;
-    const dim3 points((unsigned)((std::max(std::max(n, m), 1) + 255) / 256), 2), tiles(T / 1024, 2);
+    const int nparts = m > 0 ? std::min(kBoxBlocks, blocks_of(m, 256)) : 0;
+    const dim3 points((unsigned)blocks_of(std::max(std::max(n, m), 1), 256), 2), tiles(T / 1024, 2);
     k_icp_bbox<<<(unsigned)nparts + T / 1024, 256, 0, st>>>(so, nparts, T, inv_cell, box);
     k_icp_hash<<<1, 64, 0, st>>>(box, nparts, log2T, hash, pose_in, pose, pose_f);
     k_icp_hist<<<points, 256, 0, st>>>(so, inv_cell, hash);
