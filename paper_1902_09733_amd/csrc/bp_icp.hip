@@ -22,7 +22,8 @@
 //   2. in the same kernel, FP64 sums over the accepted pairs (count, sums of p'
 //      and q, sum of p' q^T, sum of squared distances), per block and then over
 //      the blocks in fixed orders; the queries' order (by bucket, then by
-//      source index) does not depend on the atomics of the sort either;
+//      source index; sources that can pair with nothing last) does not depend
+//      on the atomics of the sort where it matters to the sums;
 //   3. one thread: centroids and cross-covariance H, the optimal rotation by
 //      Horn's quaternion method (largest eigenvector of the symmetric 4 x 4
 //      matrix built from H, cyclic Jacobi in FP64), translation, composed
@@ -30,6 +31,7 @@
 // An iteration with fewer than 3 pairs leaves the pose unchanged.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <type_traits>
 
 #include "bp_internal.h"
@@ -101,17 +103,43 @@ __device__ __forceinline__ float icp_dist2(const float q[3], float tx, float ty,
 // the counting's atomics, whose results are each point's place in its bucket, so
 // that the records need none.  Two clouds of 256 880 points: 16 launches with
 // atomics in both passes 109 us, these 8 64 us.
+
+// Source points of a bucket up to which all are compared with all to order
+// them; a block of its own orders a larger bucket.  256 000 points, k_icp_order:
+// in buckets of 250 / 500 points 25 / 45 us, of 530 / 1000 / 4000 22 / 21 / 90.
+constexpr uint32_t kCrowd = 512;
+
 struct IcpSort {
     const float *pts;
     int n;
     uint32_t *count, *start;     // [T + 1]
-    uint32_t *tile;              // [T / 1024]
+    uint32_t *tile;              // [T / kCrowd], T / 1024 used
     uint32_t *rank;              // [n] each point's place in its bucket
     float4 *rec;
 };
 struct IcpSorts {
     IcpSort c[2];
+    // Sources that can pair with nothing whatever the pose: a coordinate that is
+    // NaN, or infinite where dmax^2 is finite (every coordinate of the moved
+    // point is then NaN or infinite).  A triangulated cloud has one per hole.
+    // They take the records after all others', in any order, since they add
+    // nothing to any sum.
+    bool inf_pairs;              // dmax^2 overflows: infinite distances are accepted
+    uint32_t *gone;              // how many there are
+    // Source buckets of more than kCrowd points, in any order.
+    uint32_t *crowded, *ncrowded;
 };
+
+__device__ __forceinline__ bool never_pairs(const IcpSorts &so, const float *q)
+{
+    bool nan = false, inf = false;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        nan |= __builtin_isnan(q[a]);
+        inf |= __builtin_isinf(q[a]);
+    }
+    return nan || (inf && !so.inf_pairs);
+}
 
 // Bounding box of the target's cells, per block: part[block][0..2] min,
 // part[block][3..5] max (INT_MAX / INT_MIN for a block without points).  The
@@ -171,11 +199,13 @@ __host__ __device__ static inline uint32_t ceil_log2(uint64_t v)
 // Bucket mapping from the bounding box: one cell of margin on each side, as
 // many bits per axis as the extent needs while they fit in log2(T), the
 // widest axes cut first when they do not.
-// The lanes also set the pose and its FP32 copy.
-__global__ void __launch_bounds__(64) k_icp_hash(const int *__restrict__ part, int nparts, uint32_t log2T,
-                                                IcpHash *__restrict__ h, const double *__restrict__ pose_in,
-                                                double *__restrict__ pose, float *__restrict__ pose_f)
+// The lanes also set the pose and its FP32 copy, and clear the sorts' counters.
+__global__ void __launch_bounds__(64) k_icp_hash(const IcpSorts so, const int *__restrict__ part, int nparts,
+                                                uint32_t log2T, IcpHash *__restrict__ h,
+                                                const double *__restrict__ pose_in, double *__restrict__ pose,
+                                                float *__restrict__ pose_f)
 {
+    if (threadIdx.x == 0) *so.gone = *so.ncrowded = 0u;
     if (threadIdx.x < 12) {
         pose[threadIdx.x] = pose_in[threadIdx.x];
         pose_f[threadIdx.x] = (float)pose_in[threadIdx.x];
@@ -221,6 +251,16 @@ __global__ void __launch_bounds__(256) k_icp_hist(const IcpSorts so, float inv_c
     if (j >= c.n) return;
     const IcpHash h = *hp;
     const float *q = c.pts + (int64_t)j * 3;
+    if (blockIdx.y == 0 && never_pairs(so, q)) {
+        // One atomic per wavefront: the counter is the same for all.
+        const uint64_t m = __ballot(true);
+        const int lane = (int)threadIdx.x & 63, first = __builtin_ctzll(m);
+        uint32_t at = 0;
+        if (lane == first) at = atomicAdd(so.gone, (uint32_t)__builtin_popcountll(m));
+        at = (uint32_t)__builtin_amdgcn_readlane((int)at, first);
+        c.rank[j] = at + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull));
+        return;
+    }
     c.rank[j] = atomicAdd(&c.count[bucket_of(h, q[0], q[1], q[2], inv_cell)], 1u);
 }
 
@@ -284,32 +324,187 @@ __global__ void __launch_bounds__(256) k_icp_scan_add(const IcpSorts so)
 // Records in bucket order, at the places the counting gave (the order inside
 // a bucket is whatever the atomics give; nothing computed from the targets'
 // records depends on it).
-__global__ void __launch_bounds__(256) k_icp_scatter(const IcpSorts so, float inv_cell, const IcpHash *__restrict__ hp)
+__global__ void __launch_bounds__(256) k_icp_scatter(const IcpSorts so, float inv_cell, const IcpHash *__restrict__ hp,
+                                                    uint32_t T)
 {
     const IcpSort &c = so.c[blockIdx.y];
     const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= c.n) return;
     const IcpHash h = *hp;
     const float *q = c.pts + (int64_t)j * 3;
-    const uint32_t b = bucket_of(h, q[0], q[1], q[2], inv_cell);
-    c.rec[c.start[b] + c.rank[j]] = make_float4(q[0], q[1], q[2], __int_as_float(j));
+    const float4 r = make_float4(q[0], q[1], q[2], __int_as_float(j));
+    const uint32_t rank = c.rank[j];
+    if (blockIdx.y == 0 && never_pairs(so, q)) {
+        c.rec[c.start[T] + rank] = r;
+        return;
+    }
+    const uint32_t b = bucket_of(h, q[0], q[1], q[2], inv_cell), s = c.start[b];
+    c.rec[s + rank] = r;
+    if (blockIdx.y == 0 && rank == 0u && c.start[b + 1] - s > kCrowd) so.crowded[atomicAdd(so.ncrowded, 1u)] = b;
 }
 
-// The records of each bucket by index: a record's place is the number of its
-// bucket's records with a smaller one (a bucket is scanned per record here, as
-// it is per query in every iteration).
-__global__ void __launch_bounds__(256) k_icp_order(const float4 *__restrict__ in, int n, float inv_cell,
-                                                  const IcpHash *__restrict__ hp, const uint32_t *__restrict__ start,
-                                                  float4 *__restrict__ out)
+// The number of w[s .. e) below `own`, four loads in flight.
+template <typename Load>
+__device__ __forceinline__ uint32_t count_below(Load load, uint32_t s, uint32_t e, int own)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
+    uint32_t below = 0;
+    for (uint32_t k = s; k < e; k += 4) {
+        int v[4];
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) v[u] = load(k + u < e ? k + u : e - 1);
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) below += k + u < e && v[u] < own;
+    }
+    return below;
+}
+
+constexpr int kOrderBlock = 1024, kCrowdBlocks = 256;
+
+// The records [s, e) of one crowded source bucket by index, in one block and
+// linear time: the index range [0, n) is cut into as many slices as the bucket
+// has records, so a slice holds at most n / records of them (and often one);
+// they are counted (`sub`), gathered slice by slice (`idx`), and a record's
+// place is its slice's first plus the slice's smaller indices.  Both arrays are
+// the bucket's own; they are read and written past the vector cache, as the
+// atomics are, and every access has ended before a barrier opens the next phase
+// (agent-scope fences instead cost 571 us for 170 buckets of 5900 points).
+__device__ void order_crowded(const float4 *__restrict__ in, uint32_t s, uint32_t e, int n, uint32_t *sub, int *idx,
+                              float4 *__restrict__ out)
+{
+    __shared__ uint32_t s_wave[kOrderBlock / 64];
+    constexpr uint32_t U = 4;                    // records of a thread in flight
+    const uint32_t c = e - s, t = threadIdx.x;
+    const int lane = (int)t & 63, wv = (int)t >> 6;
+    auto slice = [&](int i) __attribute__((always_inline)) { return (uint32_t)((uint64_t)(uint32_t)i * c / (uint32_t)n); };
+    auto get = [](const auto *p) __attribute__((always_inline)) {
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto put = [](auto *p, auto v) __attribute__((always_inline)) {
+        __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto phase = []() __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+    };
+    // Indices of the thread's next U records (-1 past the last).
+    auto indices = [&](uint32_t k0, int (&i)[U]) __attribute__((always_inline)) {
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t k = k0 + u * kOrderBlock;
+            i[u] = k < c ? __float_as_int(in[s + k].w) : -1;
+        }
+    };
+    for (uint32_t k = t; k < c; k += kOrderBlock) put(&sub[k], 0u);
+    phase();
+    for (uint32_t k0 = t; k0 < c; k0 += U * kOrderBlock) {
+        int i[U];
+        indices(k0, i);
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u)
+            if (i[u] >= 0) atomicAdd(&sub[slice(i[u])], 1u);
+    }
+    phase();
+    // Counts to first places, eight per thread and round.
+    uint32_t carry = 0;
+    for (uint32_t r0 = 0; r0 < c; r0 += 8 * kOrderBlock) {
+        uint32_t v[8], own = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) {
+            const uint32_t k = r0 + 8 * t + u;
+            v[u] = k < c ? get(&sub[k]) : 0u;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) own += v[u];
+        uint32_t incl = own;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t o = __shfl_up(incl, d, 64);
+            incl += lane >= d ? o : 0u;
+        }
+        if (lane == 63) s_wave[wv] = incl;
+        __syncthreads();
+        uint32_t before = carry, all = 0;
+#pragma unroll
+        for (int k = 0; k < kOrderBlock / 64; ++k) {
+            before += k < wv ? s_wave[k] : 0u;
+            all += s_wave[k];
+        }
+        uint32_t run = before + incl - own;
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) {
+            const uint32_t k = r0 + 8 * t + u;
+            if (k < c) put(&sub[k], run);
+            run += v[u];
+        }
+        carry += all;
+        __syncthreads();
+    }
+    phase();
+    for (uint32_t k0 = t; k0 < c; k0 += U * kOrderBlock) {
+        int i[U];
+        uint32_t at[U];
+        indices(k0, i);
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) at[u] = i[u] >= 0 ? atomicAdd(&sub[slice(i[u])], 1u) : 0u;
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u)
+            if (i[u] >= 0) put(&idx[at[u]], i[u]);
+    }
+    phase();
+    // sub[q] is now the end of slice q.
+    for (uint32_t k0 = t; k0 < c; k0 += U * kOrderBlock) {
+        int i[U];
+        uint32_t lo[U], hi[U];
+        indices(k0, i);
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t q = i[u] >= 0 ? slice(i[u]) : 0u;
+            lo[u] = q ? get(&sub[q - 1]) : 0u;
+            hi[u] = get(&sub[q]);
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u)
+            if (i[u] >= 0) {
+                const uint32_t below =
+                    count_below([&](uint32_t p) __attribute__((always_inline)) { return get(&idx[p]); }, lo[u], hi[u], i[u]);
+                out[s + lo[u] + below] = in[s + k0 + u * kOrderBlock];
+            }
+    }
+    phase();
+}
+
+// The source's records of each bucket by index: a record's place is the number
+// of its bucket's records with a smaller one.  Up to kCrowd records are compared
+// all with all; the blocks from `nb` on take the buckets with more, one block
+// each.  Records of sources that never pair stay as they are.  All of it takes
+// time linear in the points: a cloud of 256 000 with 100 000 holes costs 0.25 ms
+// for five iterations, as one without (0.22; 10.5 with every bucket compared all
+// with all), and 256 000 points in one cell 0.7 ms here (26).
+__global__ void __launch_bounds__(kOrderBlock) k_icp_order(const IcpSorts so, uint32_t T, int nb, float inv_cell,
+                                                          const IcpHash *__restrict__ hp, float4 *__restrict__ out)
+{
+    const IcpSort &c = so.c[0];
+    const float4 *in = c.rec;
+    if ((int)blockIdx.x >= nb) {
+        const uint32_t nc = *so.ncrowded;
+        for (uint32_t k = blockIdx.x - (unsigned)nb; k < nc; k += kCrowdBlocks) {
+            const uint32_t b = so.crowded[k], s = c.start[b];
+            // The counts are read no more, nor the ranks: T >= n words each.
+            order_crowded(in, s, c.start[b + 1], c.n, c.rank + s, (int *)c.count + s, out);
+        }
+        return;
+    }
+    const int i = (int)blockIdx.x * kOrderBlock + (int)threadIdx.x;
+    if (i >= c.n) return;
     const float4 r = in[i];
-    const uint32_t b = bucket_of(*hp, r.x, r.y, r.z, inv_cell), s = start[b], e = start[b + 1];
+    if ((uint32_t)i >= c.start[T]) {
+        out[i] = r;
+        return;
+    }
+    const uint32_t b = bucket_of(*hp, r.x, r.y, r.z, inv_cell), s = c.start[b], e = c.start[b + 1];
+    if (e - s > kCrowd) return;
     const int own = __float_as_int(r.w);
-    uint32_t rank = 0;
-    for (uint32_t k = s; k < e; ++k) rank += __float_as_int(in[k].w) < own;
-    out[s + rank] = r;
+    out[s + count_below([&](uint32_t k) __attribute__((always_inline)) { return __float_as_int(in[k].w); }, s, e, own)] = r;
 }
 
 // Sum over each 16-lane row in a fixed order, the same on every lane of it.
@@ -754,7 +949,7 @@ size_t icp_workspace_bytes(int n, int m)
 {
     const uint32_t T = icp_buckets(n, m);
     const size_t nb = (size_t)blocks_of(n, kIcpBlock);
-    return 2 * (align_up(((size_t)T + 1) * 4) * 2 + align_up((size_t)(T / 1024) * 4)) + align_up((size_t)m * 16) +
+    return 2 * (align_up(((size_t)T + 1) * 4) * 2 + align_up((size_t)(T / kCrowd) * 4)) + align_up((size_t)m * 16) +
            2 * align_up((size_t)n * 16) +
            align_up(nb * kIcpSums * 8 + 8) + align_up(12 * 8) + align_up(12 * 4) + align_up(kBoxBlocks * 6 * 4) +
            align_up(sizeof(IcpHash)) + align_up((size_t)n * 4) + align_up((size_t)m * 4);
@@ -773,7 +968,7 @@ bp_status launch_icp(const float *src, int n, const float *dst, int m, const dou
         c.start = (uint32_t *)p;
         p += align_up(((size_t)T + 1) * 4);
         c.tile = (uint32_t *)p;
-        p += align_up((size_t)(T / 1024) * 4);
+        p += align_up((size_t)(T / kCrowd) * 4);
     }
     float4 *rec_dst = (float4 *)p;
     p += align_up((size_t)m * 16);
@@ -805,18 +1000,26 @@ bp_status launch_icp(const float *src, int n, const float *dst, int m, const dou
     so.c[1].n = m;
     so.c[1].rec = rec_dst;
     so.c[1].rank = rank_dst;
+    // The last words of the counts, and the words of the source's tile totals,
+    // which are added up before the first bucket is listed (n points, at most
+    // T, make fewer than T / kCrowd crowded buckets).
+    so.inf_pairs = !std::isfinite(dmax2);
+    so.gone = so.c[0].count + T;
+    so.ncrowded = so.c[1].count + T;
+    so.crowded = so.c[0].tile;
     uint32_t log2T = 0;
     while ((1u << log2T) < T) ++log2T;
     const int nparts = m > 0 ? std::min(kBoxBlocks, blocks_of(m, 256)) : 0;
     const dim3 points((unsigned)blocks_of(std::max(std::max(n, m), 1), 256), 2), tiles(T / 1024, 2);
     k_icp_bbox<<<(unsigned)nparts + T / 1024, 256, 0, st>>>(so, nparts, T, inv_cell, box);
-    k_icp_hash<<<1, 64, 0, st>>>(box, nparts, log2T, hash, pose_in, pose, pose_f);
+    k_icp_hash<<<1, 64, 0, st>>>(so, box, nparts, log2T, hash, pose_in, pose, pose_f);
     k_icp_hist<<<points, 256, 0, st>>>(so, inv_cell, hash);
     k_icp_scan_tiles<<<tiles, 256, 0, st>>>(so);
     k_icp_scan_top<<<dim3(1, 2), 256, 0, st>>>(so, T / 1024);
     k_icp_scan_add<<<tiles, 256, 0, st>>>(so);
-    k_icp_scatter<<<points, 256, 0, st>>>(so, inv_cell, hash);
-    if (n > 0) k_icp_order<<<nb, 256, 0, st>>>(rec_tmp, n, inv_cell, hash, so.c[0].start, rec_src);
+    k_icp_scatter<<<points, 256, 0, st>>>(so, inv_cell, hash, T);
+    const int ob = blocks_of(n, kOrderBlock);
+    if (n > 0) k_icp_order<<<ob + kCrowdBlocks, kOrderBlock, 0, st>>>(so, T, ob, inv_cell, hash, rec_src);
     bp_status s = launch_status();
     const IcpGrid g{so.c[1].start, rec_dst, hash, inv_cell, 1.0f / inv_cell};
     for (int it = 0; it < iters && s == BP_OK; ++it) {
