@@ -167,6 +167,78 @@ __global__ void __launch_bounds__(256) k_jbu(const int32_t *__restrict__ disp, i
             den[k] = fmaf(wy, rd[k], den[k]);
         }
     }
+    if constexpr (NY > 1) {
+        // Both rows need the second evaluation below somewhere in the wavefront:
+        // in one pass over the records then, whose loads' latency bounds it with
+        // half as many wavefronts (1600 x 904, s = 8, R 4, RGB, a noisy guide: 44.0
+        // us one row after the other, 34.5 together, 35.7 with one row per thread).
+        // Together also where one row needs it: 3 to 5% slower there.
+        bool low[NY], any = false, all = true;
+#pragma unroll
+        for (int k = 0; k < NY; ++k) {
+            low[k] = !(den[k] >= 0x1p-60f);
+            any |= low[k];
+            all &= __builtin_amdgcn_ballot_w64(low[k]) != 0;
+        }
+        if (all && any) {
+            const float fx = (float)(px - s * cx) + 0.5f - 0.5f * (float)s;
+            float fy[NY], emax[NY], rm[NY], sm[NY], n2[NY], d2[NY];
+#pragma unroll
+            for (int k = 0; k < NY; ++k) {
+                fy[k] = (float)(py0 + k - s * cy) + 0.5f - 0.5f * (float)s;
+                emax[k] = -__builtin_huge_valf();
+                rm[k] = sm[k] = n2[k] = d2[k] = 0.0f;
+            }
+#pragma unroll 1
+            for (int dy = 0; dy < NT; ++dy) {
+                float sy[NY];
+#pragma unroll
+                for (int k = 0; k < NY; ++k) {
+                    const float ty = fy[k] - (float)(s * (dy - R));
+                    sy[k] = -(ty * ty * ksp);
+                }
+#pragma unroll 1
+                for (int dx = 0; dx < NT; ++dx) {
+                    const float tx = fx - (float)(s * (dx - R));
+                    const uint4 q = t_q[(oy + dy) * kMaxTap + ox + dx];
+#pragma unroll
+                    for (int k = 0; k < NY; ++k) {
+                        const float sp = sy[k] - tx * tx * ksp, r = range(k, q), e = fmaf(r, krg, sp);
+                        const bool more = e > emax[k];
+                        emax[k] = more ? e : emax[k];
+                        rm[k] = more ? r : rm[k];
+                        sm[k] = more ? sp : sm[k];
+                    }
+                }
+            }
+#pragma unroll 1
+            for (int dy = 0; dy < NT; ++dy) {
+                float sy[NY];
+#pragma unroll
+                for (int k = 0; k < NY; ++k) {
+                    const float ty = fy[k] - (float)(s * (dy - R));
+                    sy[k] = -(ty * ty * ksp);
+                }
+#pragma unroll 1
+                for (int dx = 0; dx < NT; ++dx) {
+                    const float tx = fx - (float)(s * (dx - R));
+                    const uint4 q = t_q[(oy + dy) * kMaxTap + ox + dx];
+#pragma unroll
+                    for (int k = 0; k < NY; ++k) {
+                        const float sp = sy[k] - tx * tx * ksp;
+                        const float w = __builtin_amdgcn_exp2f(fmaf(range(k, q) - rm[k], krg, sp - sm[k]));
+                        n2[k] = fmaf(w, __uint_as_float(q.w), n2[k]);
+                        d2[k] += w;
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < NY; ++k) {
+                num[k] = low[k] ? n2[k] : num[k];
+                den[k] = low[k] ? d2[k] : den[k];
+            }
+        }
+    }
 #pragma unroll
     for (int k = 0; k < NY; ++k) {
         const int py = py0 + k;
