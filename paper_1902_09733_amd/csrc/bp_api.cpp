@@ -302,7 +302,7 @@ bp_status run_one(const bp_problem &q, const Plan &pl, const bp_params &p, uint8
             // the own block, two single half-sweeps go first.
             const size_t own = pl.lv[l].msg_off, other = pl.y_off;
             const bool own_src = l < n - 1 && !first_src;
-            PairSchedule sched = pair_schedule(pl, l, K / 2, p.tau, ckpt != nullptr, own_src);
+            PairSchedule sched = pair_schedule(pl, l, K / 2, p.tau, ckpt != nullptr, own_src, false);
             if (own_src && (sched.count() & 1)) {
                 for (; t0 < 2; ++t0, ++launches) {
                     if ((st = launch_iteration(pl, l, t0, 0, p.lambda, p.tau, nullptr, variant, ws, s)) != BP_OK)
@@ -586,7 +586,7 @@ bp_status run_batched_pairs(const bp_problem *probs, int32_t count, const Plan *
     // A problem whose pairs run several per launch is a group of its own, too.
     auto schedule_of = [&](int l, int i) {
         const bool own_src = l < n - 1 && plans[i].lv[l].fmt != plans[i].lv[l + 1].fmt;
-        return pair_schedule(plans[i], l, np, p.tau, ckpt != nullptr, own_src);
+        return pair_schedule(plans[i], l, np, p.tau, ckpt != nullptr, own_src, true);
     };
     // Whether the problem's last launch reads out both colours.
     auto reads_out = [&](int i) {

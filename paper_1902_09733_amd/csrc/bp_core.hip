@@ -557,6 +557,7 @@ PairArgs make_pair_args(const Plan &p, int l, int src_kind, size_t src_off, size
     if (pairs > 1) {
         int S, R;
         pm_split(p.L, &S, &R);
+        a.near = stream_form(R, tau);
         stream_shape(&a, S, R);
     } else {
         pair_tile(v.lp, fmt_bytes(v.fmt), v.w, v.h, &a.tx, &a.ty);

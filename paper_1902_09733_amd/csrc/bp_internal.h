@@ -285,13 +285,13 @@ PairArgs make_pair_args(const Plan &p, int l, int src_kind, size_t src_off, size
 // (tiled), then `threes` of three and `twos` of two.  pair_schedule decides it
 // for level l's `np` pairs; one pair each when the launches also save states
 // for the adjoint; with even_count the number of launches is even unless np
-// is odd and all are single.
+// is odd and all are single.  batch: one of several problems of a call.
 struct PairSchedule {
     int ones, threes, twos;
     int count() const { return ones + threes + twos; }
     int pairs(int i) const { return i < ones ? 1 : i < ones + threes ? 3 : 2; }   // of launch i
 };
-PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, bool even_count);
+PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, bool even_count, bool batch);
 // Whether the finest level's last launch can read out both colours (its state
 // then stays unwritten): it streams, and nothing reads the final state.
 bool stream_reads_out(const PairSchedule &s, bool exports, bool saves);
@@ -299,6 +299,14 @@ void stream_shape(PairArgs *a, int S, int R);
 bp_status dispatch_iter_stream(const PairArgs &a, int fmt, int S, int R, hipStream_t s);
 // Window of the transform's near form: 1 (tau <= 2), 2 (tau <= 3), 0 (scans).
 inline int near_window(float tau) { return tau <= 2.0f ? 1 : tau <= 3.0f ? 2 : 0; }
+// The form a streamed launch runs with R labels per lane: above four the
+// five-label form as far as its results equal the scans', which the other
+// kernels run there (pm_transform_near2_scans), and the scans beyond.
+inline int stream_form(int R, float tau)
+{
+    const int near = near_window(tau);
+    return near == 2 && R > 4 && tau > 2.75f ? 0 : near;
+}
 // Zero the out-of-grid slots of `n` message states of each of `count`
 // problems: problem i's states are laid out like level 0 of plans[i], back to
 // back from bases[i] (checkpoint states written by the fused pairs, which

@@ -68,31 +68,47 @@ static int segment_rows(int h, int strips, int stages)
 //   676 x 380 x 64                   46.4 / 39.1 / 36.1
 //   480 x 270 x 128  (16.6 M)        44.4 / 38.9 / 43.0
 //   1352 x 760 x 128                  384 /  277 /  249
-// so for tau <= 2 two pairs from 4 M values (6 M for 16-bit rows of more than
-// four labels per lane) and three from 16 M (24 M).  The five-label form (tau
-// 2.6: 480 x 270 x 32 17.7 / 19.0, 676 x 380 x 32 30.2 / 25.2 us) needs 8 M and
-// stops at two pairs, where three spill or wait more (1352 x 760 x 128 in
-// bfloat16: 438 / 291 / 378 us), the scans (tau 5: 676 x 380 x 32 33.0 / 33.1,
-// 676 x 380 x 64 65.6 / 48; FP16 676 x 380 x 96 83 / 86) 12 M, and 32 M with
-// 16-bit rows: the more instructions a message takes, the less the memory
-// traffic that streaming saves was what held the tiled pair back.
-static int stream_pairs(const Level &v, int L, int near)
+// What a call gains (two levels, K = 8, both cost formats, labels alone, with
+// messages, and in batches of six; streamed over tiled, least and most):
+//   values               4 M        6 M        8 M       12 M       16 M       32 M
+//   tau 2    FP32     .82-1.00   .78-.93    .73-.90   .68-.90    .57-.82    .53-.79
+//     FP16, R <= 4    .96-1.09   .91-1.04   .91-.97   .88-.97    .81-.91    .72-.83
+//     FP16, R > 4    1.03-1.12   .98-1.05   .95-1.02  .93-.98    .88-.94    .78-.86
+//   tau 2.6  FP32     .92-1.09   .84-1.02   .79-.96   .72-.95    .64-.85    .56-.79
+//     FP16, R <= 4   1.00-1.17   .96-1.07   .96-1.02  .93-1.00   .86-.95    .75-.87
+//     FP16, R > 4    1.02-1.17   .98-1.08   .95-1.05  .96-1.00   .91-.97    .81-.89
+//   tau 5    FP32    1.02-1.23   .99-1.16   .92-1.06  .86-1.02   .74-.90    .66-.84
+//     FP32, R > 4    1.03-1.14   .96-1.07   .90-1.01  .82-.96    .73-.86    .66-.81
+//     FP16           1.06-1.31  1.03-1.17  1.03-1.14 1.00-1.10   .92-1.07   .81-.96
+// so two pairs from where that is about 1 (FP16, tau 2, R <= 4: from 4 M values
+// for a problem of its own, .97-1.03, and 6 M in a batch, whose small problems
+// share tiled launches, 1.02-1.09 at 4 M): the more instructions a message
+// takes, the less the memory traffic that streaming saves was what held the
+// tiled pair back.  Three pairs, the three-label form alone (elsewhere they spill
+// or wait more: 1352 x 760 x 128 in bfloat16, tau 2.6: 438 / 291 / 378 us per
+// pair), from 16 M values, and 24 M above four labels per lane: three over two,
+// 16 .. 130 M values, with five pairs (one + two + two against three + two) .78 ..
+// .97 and with six (three launches against two) .87 .. 1.03, up to 1.08 from 16 to
+// 24 M above four labels per lane.
+static int stream_pairs(const Level &v, int L, float tau, bool batch)
 {
     int S, R;
     pm_split(L, &S, &R);
-    const int nc = stream_columns(S, R);
+    const int nc = stream_columns(S, R), form = stream_form(R, tau);
     if (L != S * R || nc == 0 || v.layout != PIXEL_MAJOR) return 1;
     if (v.cost_fmt == COST_F16 && R % 4 == 0) return 1;   // those lanes hold byte costs
     const int64_t n = (int64_t)v.w * v.h * v.lp;
     const bool f32 = v.fmt == FMT_F32;
-    const int64_t two = near == 1 ? (f32 || R <= 4 ? 4000000 : 6000000) : near == 2 ? 8000000 : f32 ? 12000000 : 32000000;
+    const int64_t two = form == 1 ? (f32 ? 4000000 : R > 4 ? 8000000 : batch ? 6000000 : 4000000)
+                      : form == 2 ? (f32 || R <= 4 ? 8000000 : 10000000)
+                                  : (!f32 ? 32000000 : R <= 4 ? 12000000 : 8000000);
     if (v.w < 2 * nc || v.h < 64 || n < two) return 1;
-    return near == 1 && stream_three(R, v.fmt) && n >= (R <= 4 ? 16000000 : 24000000) ? 3 : 2;
+    return form == 1 && stream_three(R, v.fmt) && n >= (R <= 4 ? 16000000 : 24000000) ? 3 : 2;
 }
 
-PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, bool even_count)
+PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, bool even_count, bool batch)
 {
-    const int most = saves ? 1 : stream_pairs(p.lv[l], p.L, near_window(tau));
+    const int most = saves ? 1 : stream_pairs(p.lv[l], p.L, tau, batch);
     PairSchedule s{0, 0, 0};
     if (most == 3 && np >= 2) {
         // As few launches as possible.

@@ -466,9 +466,7 @@ template <int SEG, int R, typename S, int CF>
 static bp_status launch_stream_cf(const PairArgs &a, hipStream_t st)
 {
     if (a.near == 1) return launch_stream_near<SEG, R, S, CF, 1>(a, st);
-    // Five labels: with more than four per lane as far as its results equal
-    // the scans' (which the other kernels run there).
-    if (a.near == 2 && (R <= 4 || a.lt <= 2.75f * a.lambda)) return launch_stream_near<SEG, R, S, CF, 2>(a, st);
+    if (a.near == 2) return launch_stream_near<SEG, R, S, CF, 2>(a, st);
     return launch_stream_near<SEG, R, S, CF, 0>(a, st);
 }
 
