@@ -82,7 +82,10 @@ static int segment_rows(int h, int strips, int stages)
 //     FP16           1.06-1.31  1.03-1.17  1.03-1.14 1.00-1.10   .92-1.07   .81-.96
 // so two pairs from where that is about 1 (FP16, tau 2, R <= 4: from 4 M values
 // for a problem of its own, .97-1.03, and 6 M in a batch, whose small problems
-// share tiled launches, 1.02-1.09 at 4 M): the more instructions a message
+// share tiled launches, 1.02-1.09 at 4 M).  A level under a finer one starts with
+// its state out of the caches and gains earlier in 16 bits: 6 M above four labels
+// per lane and 8 M with five labels (1352 x 760 x 128, six levels, in bfloat16, tau
+// 2.6, its 8.2 M level tiled / streamed: 2760 / 2724 us).  The more instructions a message
 // takes, the less the memory traffic that streaming saves was what held the
 // tiled pair back.  Three pairs, the three-label form alone (elsewhere they spill
 // or wait more: 1352 x 760 x 128 in bfloat16, tau 2.6: 438 / 291 / 378 us per
@@ -90,7 +93,7 @@ static int segment_rows(int h, int strips, int stages)
 // 16 .. 130 M values, with five pairs (one + two + two against three + two) .78 ..
 // .97 and with six (three launches against two) .87 .. 1.03, up to 1.08 from 16 to
 // 24 M above four labels per lane.
-static int stream_pairs(const Level &v, int L, float tau, bool batch)
+static int stream_pairs(const Level &v, int L, float tau, bool finest, bool batch)
 {
     int S, R;
     pm_split(L, &S, &R);
@@ -99,8 +102,8 @@ static int stream_pairs(const Level &v, int L, float tau, bool batch)
     if (v.cost_fmt == COST_F16 && R % 4 == 0) return 1;   // those lanes hold byte costs
     const int64_t n = (int64_t)v.w * v.h * v.lp;
     const bool f32 = v.fmt == FMT_F32;
-    const int64_t two = form == 1 ? (f32 ? 4000000 : R > 4 ? 8000000 : batch ? 6000000 : 4000000)
-                      : form == 2 ? (f32 || R <= 4 ? 8000000 : 10000000)
+    const int64_t two = form == 1 ? (f32 ? 4000000 : R > 4 ? (finest ? 8000000 : 6000000) : finest && batch ? 6000000 : 4000000)
+                      : form == 2 ? (f32 || R <= 4 || !finest ? 8000000 : 10000000)
                                   : (!f32 ? 32000000 : R <= 4 ? 12000000 : 8000000);
     if (v.w < 2 * nc || v.h < 64 || n < two) return 1;
     return form == 1 && stream_three(R, v.fmt) && n >= (R <= 4 ? 16000000 : 24000000) ? 3 : 2;
@@ -108,7 +111,7 @@ static int stream_pairs(const Level &v, int L, float tau, bool batch)
 
 PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, bool even_count, bool batch)
 {
-    const int most = saves ? 1 : stream_pairs(p.lv[l], p.L, tau, batch);
+    const int most = saves ? 1 : stream_pairs(p.lv[l], p.L, tau, l == 0, batch);
     PairSchedule s{0, 0, 0};
     if (most == 3 && np >= 2) {
         // As few launches as possible.
@@ -140,7 +143,8 @@ PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, 
 // The extra stage against colour 0's state stored and a readout pass over it,
 // whole frames: 676 x 380 x 64 FP32 454 -> 431 us, 1352 x 760 x 128 FP32 2591 ->
 // 2327, in bfloat16 with soft disparities 2823 -> 2758, eight frames in FP16
-// 5368 -> 5267.
+// 5368 -> 5267.  Over all splits, forms and costs at 1352 x 760: FP32 .78 to .95 of
+// the time, also where its registers spill, bfloat16 .95 to 1.00.
 bool stream_reads_out(const PairSchedule &s, bool exports, bool saves)
 {
     return !exports && !saves && s.count() > 0 && s.pairs(s.count() - 1) > 1;
