@@ -584,9 +584,16 @@ bp_status run_batched_pairs(const bp_problem *probs, int32_t count, const Plan *
     // 60 MB to 2 GB: letting all those above the budget share launches was
     // 1-3% slower than one after the other).
     // A problem whose pairs run several per launch is a group of its own, too.
+    auto working_set = [&](int l, int i) {
+        const Level &v = plans[i].lv[l];
+        return v.cost_bytes + v.msg_bytes + (size_t)4 * v.blk * fmt_bytes(v.fmt);
+    };
+    auto share = [&](int l, int i, int j) {   // neighbours that fit one group
+        return j >= 0 && j < count && cls_of[i] == cls_of[j] && working_set(l, i) + working_set(l, j) <= kPairGroupBytes;
+    };
     auto schedule_of = [&](int l, int i) {
         const bool own_src = l < n - 1 && plans[i].lv[l].fmt != plans[i].lv[l + 1].fmt;
-        return pair_schedule(plans[i], l, np, p.tau, ckpt != nullptr, own_src, true);
+        return pair_schedule(plans[i], l, np, p.tau, ckpt != nullptr, own_src, share(l, i, i - 1) || share(l, i, i + 1));
     };
     // Whether the problem's last launch reads out both colours.
     auto reads_out = [&](int i) {
@@ -597,8 +604,7 @@ bp_status run_batched_pairs(const bp_problem *probs, int32_t count, const Plan *
         int g = 0;
         size_t acc = 0;
         for (int i = 0; i < count; ++i) {
-            const Level &v = plans[i].lv[l];
-            const size_t wsz = v.cost_bytes + v.msg_bytes + (size_t)4 * v.blk * fmt_bytes(v.fmt);
+            const size_t wsz = working_set(l, i);
             const bool alone = schedule_of(l, i).count() < np;
             if (acc > 0 && (alone || acc + wsz > kPairGroupBytes)) {
                 ++g;

@@ -285,13 +285,14 @@ PairArgs make_pair_args(const Plan &p, int l, int src_kind, size_t src_off, size
 // (tiled), then `threes` of three and `twos` of two.  pair_schedule decides it
 // for level l's `np` pairs; one pair each when the launches also save states
 // for the adjoint; with even_count the number of launches is even unless np
-// is odd and all are single.  batch: one of several problems of a call.
+// is odd and all are single.  shared: tiled, the launches would be shared with
+// another problem of the call.
 struct PairSchedule {
     int ones, threes, twos;
     int count() const { return ones + threes + twos; }
     int pairs(int i) const { return i < ones ? 1 : i < ones + threes ? 3 : 2; }   // of launch i
 };
-PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, bool even_count, bool batch);
+PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, bool even_count, bool shared);
 // Whether the finest level's last launch can read out both colours (its state
 // then stays unwritten): it streams, and nothing reads the final state.
 bool stream_reads_out(const PairSchedule &s, bool exports, bool saves);

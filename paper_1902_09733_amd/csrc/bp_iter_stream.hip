@@ -80,12 +80,13 @@ static int segment_rows(int h, int strips, int stages)
 //   tau 5    FP32    1.02-1.23   .99-1.16   .92-1.06  .86-1.02   .74-.90    .66-.84
 //     FP32, R > 4    1.03-1.14   .96-1.07   .90-1.01  .82-.96    .73-.86    .66-.81
 //     FP16           1.06-1.31  1.03-1.17  1.03-1.14 1.00-1.10   .92-1.07   .81-.96
-// so two pairs from where that is about 1 (FP16, tau 2, R <= 4: from 4 M values
-// for a problem of its own, .97-1.03, and 6 M in a batch, whose small problems
-// share tiled launches, 1.02-1.09 at 4 M).  A level under a finer one starts with
-// its state out of the caches and gains earlier in 16 bits: 6 M above four labels
-// per lane and 8 M with five labels (1352 x 760 x 128, six levels, in bfloat16, tau
-// 2.6, its 8.2 M level tiled / streamed: 2760 / 2724 us).  The more instructions a message
+// so two pairs from where that is about 1 (FP16, tau 2, R <= 4: from 4 M values,
+// .97-1.03, and 6 M where several problems of a batch share tiled launches,
+// 1.02-1.09 at 4 M; R > 4: 353 x 236 x 96, 8.0 M, 141 -> 136 us, 340 x 213 x 96, 7.0
+// M, 220 -> 223).  A level under a finer one starts with its state out of the
+// caches and gains earlier in 16 bits above four labels per lane, from 6 M, with
+// five labels from 8 M (1352 x 760 x 128, six levels, in bfloat16, tau 2.6, its
+// 8.2 M level tiled / streamed: 2760 / 2724 us).  The more instructions a message
 // takes, the less the memory traffic that streaming saves was what held the
 // tiled pair back.  Three pairs, the three-label form alone (elsewhere they spill
 // or wait more: 1352 x 760 x 128 in bfloat16, tau 2.6: 438 / 291 / 378 us per
@@ -93,7 +94,7 @@ static int segment_rows(int h, int strips, int stages)
 // 16 .. 130 M values, with five pairs (one + two + two against three + two) .78 ..
 // .97 and with six (three launches against two) .87 .. 1.03, up to 1.08 from 16 to
 // 24 M above four labels per lane.
-static int stream_pairs(const Level &v, int L, float tau, bool finest, bool batch)
+static int stream_pairs(const Level &v, int L, float tau, bool finest, bool shared)
 {
     int S, R;
     pm_split(L, &S, &R);
@@ -102,16 +103,16 @@ static int stream_pairs(const Level &v, int L, float tau, bool finest, bool batc
     if (v.cost_fmt == COST_F16 && R % 4 == 0) return 1;   // those lanes hold byte costs
     const int64_t n = (int64_t)v.w * v.h * v.lp;
     const bool f32 = v.fmt == FMT_F32;
-    const int64_t two = form == 1 ? (f32 ? 4000000 : R > 4 ? (finest ? 8000000 : 6000000) : finest && batch ? 6000000 : 4000000)
+    const int64_t two = form == 1 ? (f32 ? 4000000 : R > 4 ? (finest ? 7500000 : 6000000) : finest && shared ? 6000000 : 4000000)
                       : form == 2 ? (f32 || R <= 4 || !finest ? 8000000 : 10000000)
                                   : (!f32 ? 32000000 : R <= 4 ? 12000000 : 8000000);
     if (v.w < 2 * nc || v.h < 64 || n < two) return 1;
     return form == 1 && stream_three(R, v.fmt) && n >= (R <= 4 ? 16000000 : 24000000) ? 3 : 2;
 }
 
-PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, bool even_count, bool batch)
+PairSchedule pair_schedule(const Plan &p, int l, int np, float tau, bool saves, bool even_count, bool shared)
 {
-    const int most = saves ? 1 : stream_pairs(p.lv[l], p.L, tau, l == 0, batch);
+    const int most = saves ? 1 : stream_pairs(p.lv[l], p.L, tau, l == 0, shared);
     PairSchedule s{0, 0, 0};
     if (most == 3 && np >= 2) {
         // As few launches as possible.

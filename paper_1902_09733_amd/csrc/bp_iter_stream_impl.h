@@ -18,22 +18,30 @@
 // between stages (`up` for the pixel above, handled at the next step; `dn` and
 // the older `dd` for the one below, handled three steps on); messages left and
 // right go to the neighbouring columns' lane groups through LDS, one row per
-// stage boundary, column and side, read at the head of the step that
-// handles their receiver (a barrier, then the step's writes, a barrier).
+// stage boundary, column and side.  A row that stage s writes in step n is read
+// by its owner at the end of step n + 1, for stage s + 1 in step n + 2, and
+// written again in step n + 2.  One barrier closes each step, so the read of a
+// row lies between two barriers with neither of its writes.
 //
-// Edges: a strip's block carries T - 1 more columns on each side and a
-// segment T - 1 more rows, and stage s covers the strip and segment plus
-// T - s; what lies beyond is garbage that no covered pixel reads.  Only stage
-// T writes memory, and each slot of colour 0 has one writer.  As in the tiled
+// Edges: with NS stages (T, and one more in a launch that reads out both
+// colours) a strip's block carries NS - 1 more columns on each side and a
+// segment NS - 1 more rows, and stage s covers the strip and segment plus
+// NS - s; what lies beyond is garbage that no covered pixel reads.  Only stage
+// T writes the state (none does where both colours are read out), and each
+// slot of colour 0 has one writer.  As in the tiled
 // pair colour 0's incoming rows are double-buffered (`src`, `dst`), the first
 // launch of a level reads the parent level's state or zeros, and the launch
 // that ends a level stores colour 1's incoming rows (write_c1), which stage T
 // holds as its inputs.
 //
-// What bounds it: with four labels per lane instruction issue (about 150 VALU
-// instructions per visit of four pixels, 80% of the issue slots taken at
-// 676 x 380 x 64), with eight and FP32 rows memory (5.3 TB/s with the strips'
-// repeated columns).  A step's loads are issued two steps (stage 1) or one
+// What bounds it, by counters (VALU instructions against the 614 G wavefront
+// instructions a second of the nominal clock; HBM bytes): with four labels per
+// lane instruction issue (676 x 380 x 64, byte costs: .72 to .74 of the slots, .82
+// to .88 of those in the CUs' busy cycles, 2.7 to 2.9 TB/s; about 150 VALU
+// instructions per visit of four pixels), with eight and 16-bit rows too (1352 x
+// 760 x 128, five labels: .80 and .96, 3.7 TB/s); with eight and FP32 rows issue
+// and memory together (.58 and .71, 4.6 TB/s; levels 1 and 2, FP32 costs, .32 to
+// .51 and 4.8 to 6.1 TB/s).  A step's loads are issued two steps (stage 1) or one
 // step (costs) ahead, without branches, so that the compiler's waits count
 // just them; before that, waits for whole queues (stores included) took half
 // the time (1352 x 760 x 128: 2.11 against 1.43 ms for its six pairs).
@@ -43,7 +51,9 @@
 //
 // Messages are rounded to the storage format where the one-half-sweep kernel
 // stores them, and the arithmetic per message is that kernel's variant 1
-// (bp_pm_core.h), so results are equal bit for bit.
+// (bp_pm_core.h), so results are equal bit for bit; with the five-label form
+// above four labels per lane, whose results are the scans' while h stays below
+// about 2^18 lambda (pm_transform_near2_scans), up to roundings of h beyond.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -174,7 +184,11 @@ constexpr uint32_t kNowhere = 0xffffff00u;
 // stores its rows when asked); 3 the same where nothing reads the final state:
 // it reads out colour 0 too, in one more stage, and stores labels only (a
 // readout pass reads colour 0's state and costs: 21 us at 676 x 380 x 64 and
-// 215 at 1352 x 760 x 128, in FP32).
+// 215 at 1352 x 760 x 128, in FP32).  The extra stage's registers spill a few in
+// some forms (three pairs at 16 and 32 labels, FP32 costs at 128 labels with
+// tau > 2) and it is the faster end there too: whole calls at 1352 x 760, two
+// levels, against the pass, FP32 at 16 .. 128 labels and tau 2 .. 5 .78 to .95 of the
+// time, bfloat16 .95 to 1.00.
 template <int SEG, int R, typename S, int P, int NW, int CF, int NEAR, int END>
 __global__ void __launch_bounds__(NW * 64) k_iter_stream(const PairArgs a)
 {

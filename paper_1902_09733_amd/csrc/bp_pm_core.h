@@ -116,7 +116,9 @@ __device__ __forceinline__ void pm_transform_near(float (&h)[R], int s, int f0, 
 // h(g) + lambda |f - g| >= min h + lt + lambda / 4, more than the truncation
 // cap by far more than its own rounding as long as h stays below about
 // 2^18 lambda, so it never is the minimum: the results equal the scans' bit
-// for bit.  With eight labels per lane about 70 instructions per message
+// for bit.  Beyond, a message may differ from the scans' by roundings of h (the
+// scans' far candidates then round down to the cap or below); over h / lambda
+// from 2^11 to 2^28 the messages' largest and mean error was no larger.  With eight labels per lane about 70 instructions per message
 // against 96.
 template <int SEG, int R>
 __device__ __forceinline__ void pm_transform_near2_scans(const float (&h)[R], int s, float lam, float lt,

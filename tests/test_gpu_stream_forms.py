@@ -12,11 +12,18 @@ pair just below them.
 The arithmetic per message is variant 1's, so labels, soft-argmin disparities and
 final messages agree bit for bit on real-valued costs: tolerance 0; with messages
 out (the last launch stores the state) and without (it reads out both colours).
+
+Where lambda is below h / 2^18 the five-label form above four labels per lane may
+differ from the scans by roundings of h: there its messages' largest error against
+the FP64 oracle is at most the scans', and the mean within a thousandth of theirs.
 """
 import ctypes
 
+import numpy as np
 import pytest
 import torch
+
+import oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -58,7 +65,7 @@ CASES = [
     # One pair per launch below the lines.
     (64, 241, 257, 1, 4, "f32", 2.0, [1, 1]),
     (64, 241, 257, 2, 8, "f16", 2.0, [1, 1, 1, 1]),
-    (96, 283, 281, 2, 8, "f16", 2.0, [1, 1, 1, 1]),
+    (96, 269, 281, 2, 8, "f16", 2.0, [1, 1, 1, 1]),
     (96, 289, 341, 2, 8, "bf16", 2.6, [1, 1, 1, 1]),
     (96, 271, 301, 1, 4, "f32", 2.9, [1, 1]),
     (96, 451, 461, 2, 8, "f16", 2.9, [1, 1, 1, 1]),
@@ -104,3 +111,22 @@ def test_forms(dev, L, H, W, levels, K, fmt, tau, pairs):
     torch.cuda.synchronize()
     for k in ("disp", "soft"):
         assert torch.equal(out[k], ref[k]), k
+
+
+@pytest.mark.parametrize("L,H,W", [(96, 293, 301), (128, 241, 289)])
+@pytest.mark.parametrize("low,span,lam", [(0.0, 20.0, 1e-7), (0.0, 20.0, 1e-5), (15.0, 0.05, 1e-6), (15.0, 0.05, 2e-5),
+                                          (15.0, 0.05, 1e-3)])
+def test_five_labels_at_small_lambda(dev, L, H, W, low, span, lam):
+    import paper_1902_09733_amd as bp
+    g = torch.Generator(device="cuda")
+    g.manual_seed(L + H)
+    cost = low + span * torch.rand((L, H, W), generator=g, device=dev)
+    p = [bp.BPParams(levels=1, iters=4, lam=lam, tau=2.6, variant=v) for v in (0, 1)]
+    assert launches(cost, p[0], dev) == [2]
+    out = [bp.run(cost, q, want_msgs=True)["msgs"].cpu().numpy() for q in p]
+    ref = oracle.run(cost.cpu().numpy().astype(np.float64), 1, 4, float(np.float32(lam)), float(np.float32(2.6)),
+                     want_msgs=True)["msgs"]
+    e = [np.abs(o - ref) for o in out]
+    print(f"L={L} lam={lam}: largest error {e[0].max():.3e} / {e[1].max():.3e}, mean {e[0].mean():.4e} / {e[1].mean():.4e}",
+          flush=True)
+    assert e[0].max() <= e[1].max() and e[0].mean() <= 1.001 * e[1].mean()
