@@ -338,9 +338,11 @@ typedef struct {
                                label of the level (mb = msg_bytes): a single half-sweep
                                (4 + 8 mb) / 2 (the active half reads its cost and four incoming
                                rows and writes four outgoing ones); a launch of one or more fused
-                               pairs 4 + 4 mb (both colours' costs, colour 0's rows read and
+                               pairs cb + 4 mb (both colours' costs, cb = 4 bytes or at the finest
+                               level of a pair 2 or 1 where it is kept so; colour 0's rows read and
                                written once), plus 2 mb when it ends a level and stores colour
-                               1's rows */
+                               1's rows; cb + 2 mb for a last launch that reads out both colours
+                               and stores no state */
 } bp_launch_record;
 
 /*

@@ -130,3 +130,19 @@ def test_five_labels_at_small_lambda(dev, L, H, W, low, span, lam):
     print(f"L={L} lam={lam}: largest error {e[0].max():.3e} / {e[1].max():.3e}, mean {e[0].mean():.4e} / {e[1].mean():.4e}",
           flush=True)
     assert e[0].max() <= e[1].max() and e[0].mean() <= 1.001 * e[1].mean()
+
+
+def test_batch_on_both_sides_of_the_shared_line(dev):
+    """16-bit problems of 4 to 6 M values: neighbours of one lane split that share tiled launches, one whose
+    neighbours are of other splits (streamed), and one above the line, against each alone with single half-sweeps."""
+    import paper_1902_09733_amd as bp
+    g = torch.Generator(device="cuda")
+    g.manual_seed(8)
+    costs = [20.0 * torch.rand((L, h, w), generator=g, device=dev)
+             for L, h, w in [(64, 241, 281), (64, 239, 277), (96, 100, 120), (64, 251, 263), (128, 90, 111), (64, 311, 331)]]
+    p = [bp.BPParams(levels=2, iters=8, lam=7.3, tau=2.0, msg_dtype="f16", variant=v, temperature=0.7) for v in (0, 1)]
+    outs = bp.run(costs, p[0], want_soft=True, want_msgs=True)
+    for c, o in zip(costs, outs):
+        r = bp.run(c, p[1], want_soft=True, want_msgs=True)
+        torch.cuda.synchronize()
+        assert all(torch.equal(o[k], r[k]) for k in ("disp", "soft", "msgs")), tuple(c.shape)
