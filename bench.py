@@ -30,6 +30,8 @@ sys.path.insert(0, ROOT)
 
 METRIC = "BP updates/s (pixel·label·iter), pairs/s at 676x380x64; HBM GB/s vs peak"
 HBM_PEAK_GBS = 8000.0
+# 256 CUs x 4 SIMDs, one wavefront's VALU instruction in 4 cycles each, at 2.4 GHz.
+VALU_PEAK_GIPS = 614.4
 
 
 def parse():
@@ -192,13 +194,26 @@ def main():
     # one-half-sweep kernel would have to stream to match this time.
     equiv = lv_units[0] * (4.0 + 8.0 * (4 if args.msg_dtype == "f32" else 2)) / 2.0 / (l0_ms * 1e-3) / 1e9
 
+    # Streamed launches are bound by instruction issue: their VALU instructions
+    # (counted once, valid while the sources are unchanged) over the time, against
+    # the issue rate; the others by HBM.
+    streamed = lv_units[0] > 2.5 * w * h * L
+    headline = args.msg_dtype == "f32" and not args.volume
+    counted = stored_counters("k_iter_stream") if streamed and headline else None
+    bound = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+             "frac": round(achieved / HBM_PEAK_GBS, 4)}
+    if counted:
+        issue = float(counted["valu_per_launch"]) / (l0_ms * 1e-3) / 1e9
+        bound = {"bound": "valu issue", "achieved": round(issue, 1), "peak": VALU_PEAK_GIPS,
+                 "unit": "G wavefront instructions/s", "frac": round(issue / VALU_PEAK_GIPS, 4),
+                 "hbm_GBps": round(achieved, 1), "hbm_frac": round(achieved / HBM_PEAK_GBS, 4)}
+
     roofline = {
-        "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-        "frac": round(achieved / HBM_PEAK_GBS, 4),
-        "traffic": stored_traffic("k_iter_pm2") if fused and lv_units[0] <= 2.5 * w * h * L and args.msg_dtype == "f32"
-        else None,
+        **bound,
+        "traffic": stored_traffic("k_iter_stream") if counted else
+        stored_traffic("k_iter_pm2") if fused and not streamed and headline else None,
         "kernel": (f"k_iter_stream level-0 launches of several pairs of checkerboard half-sweeps ({w}x{h}x{L}, "
-                   f"{args.msg_dtype} messages)") if lv_units[0] > 2.5 * w * h * L else
+                   f"{args.msg_dtype} messages)") if streamed else
                   (f"k_iter_pm2 level-0 fused pair of checkerboard half-sweeps ({w}x{h}x{L}, {args.msg_dtype} "
                    "messages)") if fused else
                   f"k_iter_pm level-0 checkerboard half-sweep ({w}x{h}x{L}, {args.msg_dtype} messages)",
@@ -519,6 +534,11 @@ TRAFFIC = {
                    ["paper_1902_09733_amd/csrc/bp_iter_pm2_impl.h", "paper_1902_09733_amd/csrc/bp_iter_pm2_f32.hip",
                     "paper_1902_09733_amd/csrc/bp_pm_core.h", "paper_1902_09733_amd/csrc/bp_device.h",
                     "paper_1902_09733_amd/csrc/bp_internal.h"]),
+    "k_iter_stream": ("traffic_k_iter_stream_aerial676x380_L64_f32.txt",
+                      ["paper_1902_09733_amd/csrc/bp_iter_stream_impl.h", "paper_1902_09733_amd/csrc/bp_iter_stream.h",
+                       "paper_1902_09733_amd/csrc/bp_iter_stream.hip",
+                       "paper_1902_09733_amd/csrc/bp_iter_stream_f32.hip", "paper_1902_09733_amd/csrc/bp_pm_core.h",
+                       "paper_1902_09733_amd/csrc/bp_device.h", "paper_1902_09733_amd/csrc/bp_internal.h"]),
 }
 
 
@@ -536,6 +556,12 @@ def stored_traffic(kernel="k_iter_pm2"):
     passes (FETCH_SIZE + WRITE_SIZE, each scaled by the same counter's reading
     for a plain copy of known size), or None when the kernel sources changed
     since the counters were taken."""
+    kv = stored_counters(kernel)
+    return float(kv["fetch_bytes_per_launch"]) + float(kv["write_bytes_per_launch"]) if kv else None
+
+
+def stored_counters(kernel):
+    """The committed counters of `kernel` per level-0 launch, or None when its sources changed since."""
     try:
         with open(os.path.join(ROOT, "profiles", TRAFFIC[kernel][0])) as fh:
             kv = dict(line.split(None, 1) for line in fh if line.strip() and not line.startswith("#"))
@@ -543,7 +569,7 @@ def stored_traffic(kernel="k_iter_pm2"):
         return None
     if kv.get("sources_sha256", "").strip() != sources_digest(kernel):
         return None
-    return float(kv["fetch_bytes_per_launch"]) + float(kv["write_bytes_per_launch"])
+    return kv
 
 
 def form_points(args):
