@@ -173,14 +173,9 @@ __global__ void __launch_bounds__(256) k_jbu(const int32_t *__restrict__ disp, i
         // half as many wavefronts (1600 x 904, s = 8, R 4, RGB, a noisy guide: 44.0
         // us one row after the other, 34.5 together, 35.7 with one row per thread).
         // Together also where one row needs it: 3 to 5% slower there.
-        bool low[NY], any = false, all = true;
-#pragma unroll
-        for (int k = 0; k < NY; ++k) {
-            low[k] = !(den[k] >= 0x1p-60f);
-            any |= low[k];
-            all &= __builtin_amdgcn_ballot_w64(low[k]) != 0;
-        }
-        if (all && any) {
+        const bool low[2] = {!(den[0] >= 0x1p-60f), !(den[1] >= 0x1p-60f)};
+        static_assert(NY == 2, "rows of a cell per thread");
+        if ((low[0] || low[1]) && __any(low[0]) && __any(low[1])) {
             const float fx = (float)(px - s * cx) + 0.5f - 0.5f * (float)s;
             float fy[NY], emax[NY], rm[NY], sm[NY], n2[NY], d2[NY];
 #pragma unroll
