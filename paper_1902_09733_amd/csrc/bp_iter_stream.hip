@@ -94,6 +94,10 @@ static int segment_rows(int h, int strips, int stages)
 // 16 .. 130 M values, with five pairs (one + two + two against three + two) .78 ..
 // .97 and with six (three launches against two) .87 .. 1.03, up to 1.08 from 16 to
 // 24 M above four labels per lane.
+// Label counts that fill the lanes only (16, 32, 64, 96, 128): the others are
+// padded to these, and the masks that their padded labels need are not compiled
+// into the streamed kernel; above 128 (12 and 16 labels per lane) its messages
+// would not fit the registers.
 static int stream_pairs(const Level &v, int L, float tau, bool finest, bool shared)
 {
     int S, R;
